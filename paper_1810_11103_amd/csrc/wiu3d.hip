@@ -45,23 +45,35 @@ WIU_DEV long long u3idx(const Dims3& d, int i, int j, int k) {
 // backward difference at the clamped node) -- so differences of nearby
 // positions take the base difference error-free.
 // ===========================================================================
-WIU_DEV void c3_point(const Dims3& d, const double* __restrict__ X, int c, const int p_in[3], double& base,
-                      double& off) {
-  int p[3] = {p_in[0], p_in[1], p_in[2]};
-  off = 0.0;
-  int cc[3], in[3], e[3];
+// The index part, the same for the three coordinates: the clamped node, the
+// distance beyond it and the step inward per direction, and the periods
+// crossed.
+struct Pos3 {
+  int cc[3], in[3], e[3], turns[3];
+};
+WIU_DEV Pos3 c3_pos(const Dims3& d, const int p_in[3]) {
+  Pos3 r;
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
+    int p = p_in[a];
+    r.turns[a] = 0;
     if (d.bc[a] == WIU_BC_PERIODIC) {
-      const int w = bc_index(p[a], d.n[a], 0);
-      if (a == c) off += (double)((p[a] - w) / d.n[a]) * d.L[a];
-      p[a] = w;
+      const int w = bc_index(p, d.n[a], 0), by = p - w;
+      r.turns[a] = by == 0 ? 0 : (by == d.n[a] ? 1 : (by == -d.n[a] ? -1 : by / d.n[a]));
+      p = w;
     }
-    cc[a] = min(max(p[a], 0), d.n[a] - 1);
-    e[a] = abs(p[a] - cc[a]);
-    in[a] = e[a] ? (p[a] < 0 ? 1 : -1) : 0;
+    r.cc[a] = min(max(p, 0), d.n[a] - 1);
+    r.e[a] = abs(p - r.cc[a]);
+    r.in[a] = r.e[a] ? (p < 0 ? 1 : -1) : 0;
   }
+  return r;
+}
+
+WIU_DEV void c3_at(const Dims3& d, const double* __restrict__ X, int c, const Pos3& r, double& base, double& off) {
+  off = (c == 0 ? r.turns[0] * d.L[0] : (c == 1 ? r.turns[1] * d.L[1] : r.turns[2] * d.L[2]));
+  const int* e = r.e;
   auto at = [&](int da, int db, int dc) {
-    return X[((long long)(cc[2] + dc) * d.n[1] + (cc[1] + db)) * d.n[0] + (cc[0] + da)];
+    return X[((long long)(r.cc[2] + dc) * d.n[1] + (r.cc[1] + db)) * d.n[0] + (r.cc[0] + da)];
   };
   base = at(0, 0, 0);
   if (e[0] | e[1] | e[2]) {
@@ -74,7 +86,7 @@ WIU_DEV void c3_point(const Dims3& d, const double* __restrict__ X, int c, const
       for (int s = 0; s < 8; ++s) {
         if ((s & ~t) != 0) continue;  // s a subset of t
         const int s0 = s & 1, s1 = (s >> 1) & 1, s2 = (s >> 2) & 1;
-        const double v = at(s0 * in[0], s1 * in[1], s2 * in[2]);
+        const double v = at(s0 * r.in[0], s1 * r.in[1], s2 * r.in[2]);
         md += ((s0 + s1 + s2) & 1) ? -v : v;
       }
       ext += (double)((t0 ? e[0] : 1) * (t1 ? e[1] : 1) * (t2 ? e[2] : 1)) * md;
@@ -85,8 +97,8 @@ WIU_DEV void c3_point(const Dims3& d, const double* __restrict__ X, int c, const
 
 WIU_DEV double c3_diff(const Dims3& d, const double* X, int c, const int p1[3], const int p0[3]) {
   double b1, o1, b0, o0, s, e;
-  c3_point(d, X, c, p1, b1, o1);
-  c3_point(d, X, c, p0, b0, o0);
+  c3_at(d, X, c, c3_pos(d, p1), b1, o1);
+  c3_at(d, X, c, c3_pos(d, p0), b0, o0);
   two_sum(b1, -b0, s, e);
   return s + ((o1 - o0) + e);
 }
@@ -95,100 +107,389 @@ struct Coord3 {
   const double* x[3];
 };
 
-// Inner derivatives D_a x_c (a, c = 0..2) on the box [-E, n+E)^3:
-// Dx[3a + c][box index].
-__global__ void m3_inner_kernel(Dims3 d, MetricStencil ms, int E, Coord3 X, double* __restrict__ Dx) {
-  const long long W0 = d.n[0] + 2 * E, W1 = d.n[1] + 2 * E, W2 = d.n[2] + 2 * E;
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long P = W0 * W1 * W2;
-  if (t >= P) return;
-  const int p[3] = {(int)(t % W0) - E, (int)((t / W0) % W1) - E, (int)(t / (W0 * W1)) - E};
-  for (int a = 0; a < 3; ++a)
+// ===========================================================================
+// Metrics: four kernels over boxes of nodes around the grid.
+//   m3_ext_kernel    the extended coordinates, each once, as hi + lo
+//   m3_inner_kernel  the nine inner derivatives D_a x_c
+//   m3_nodal_kernel  the nine nodal metrics (Eq. 2.4) and J^{-1} (Eq. 2.5)
+//   m3_band_kernel   the stored planes and their midpoint interpolation
+// K is the reach of the scheme's central operator (3 .. 7).  Along a bounded
+// direction the nodal box is the band B the interpolation needs, along a
+// periodic one the grid alone (the band kernel wraps its reads, so band
+// copies are the nodal values); the inner box is K wider, the coordinates K
+// wider again.  The boundary rule is thus applied once per position, and the
+// stencils behind it are plain accesses at constant strides.  150 x 131 x 117
+// periodic, WENOIU5-2MP: 651 us (ext 46, inner 151, nodal 257, band 197),
+// bound by the L2 traffic of the stencils and, in the nodal kernel, by LDS
+// reads and issue alike; 4818 us (inner 643, nodal 3961, band 214) when every
+// tap applied the rule to both of its ends.
+// Scratch arrays are stored row by row, the components of a row next to each
+// other ([k][j][component][i]): a stencil tap then touches one stretch of
+// memory for all its components instead of one page for each.
+// ===========================================================================
+struct Box3 {
+  int h[3];         // halo beyond the grid, per direction
+  int w[3];         // widths n + 2 h
+  int off, pitch;   // slot of i = 0 in a row and slots of a row, multiples of 16 (whole cache lines)
+  long long P;      // slots: pitch w[1] w[2]
+};
+
+// Offset of node (i, j, k) in an array of nc components, and its strides
+// along i, j and k (components are one pitch apart).
+WIU_DEV long long b3idx(const Box3& b, int nc, int i, int j, int k) {
+  return ((long long)(k + b.h[2]) * b.w[1] + (j + b.h[1])) * nc * b.pitch + (i + b.off);
+}
+WIU_DEV void b3strides(const Box3& b, int nc, long long st[3]) {
+  st[0] = 1;
+  st[1] = (long long)nc * b.pitch;
+  st[2] = st[1] * b.w[1];
+}
+
+// The node of a thread.  A block is 256 consecutive nodes of a plane (i, then
+// j); `grp` consecutive blocks (about B3_ROWS rows) form a slab whose planes
+// follow each other, in XCD-aware order.  The blocks an XCD works on at a time
+// then span a few rows of many planes, so that the stencils along j and k
+// find their operands in its L2.
+constexpr int B3_ROWS = 16;
+WIU_DEV bool b3_node(const Box3& b, int& i, int& j, int& k) {
+  const int plane = b.w[0] * b.w[1], per = (plane + 255) >> 8;
+  const int grp = min(per, max(1, (B3_ROWS * b.w[0]) >> 8));
+  const int lid = xcd_remap(blockIdx.x, gridDim.x);
+  const int slab = lid / (grp * b.w[2]);
+  const int rest = lid - slab * grp * b.w[2];
+  const int g = min(grp, per - slab * grp);  // the last slab may hold fewer blocks
+  const int z = rest / g;
+  const int r = (slab * grp + rest - z * g) * 256 + threadIdx.x;
+  if (r >= plane) return false;
+  const int y = r / b.w[0];
+  i = r - y * b.w[0] - b.h[0]; j = y - b.h[1]; k = z - b.h[2];
+  return true;
+}
+
+// Tile of the derivative kernels: 16 x 8 x 4 nodes.
+constexpr int T3_X = 16, T3_Y = 8, T3_Z = 4;
+
+// Whether the positions within `reach` of (i, j, k) are nodes of the grid
+// (their lo parts are exactly zero there and are not read).
+WIU_DEV bool inside3(const Dims3& d, int i, int j, int k, int reach) {
+  return i >= reach && i < d.n[0] - reach && j >= reach && j < d.n[1] - reach && k >= reach && k < d.n[2] - reach;
+}
+
+// Coordinates on the box, as the unevaluated sum hi + lo of node coordinate
+// and offset (exact): components 0..2 hi, 3..5 lo.  A difference of two
+// positions is (hi1 - hi0) + (lo1 - lo0), which keeps its digits across a
+// seam.  Only tiles that reach beyond an end read lo parts, none of a node
+// 2 K + T3_X or more from every end, where they are not written.
+__global__ void __launch_bounds__(256) m3_ext_kernel(Dims3 d, Box3 bx, int K, Coord3 X, double* __restrict__ XE) {
+  int p[3];
+  if (!b3_node(bx, p[0], p[1], p[2])) return;
+  double* xe = XE + b3idx(bx, 6, p[0], p[1], p[2]);
+  const bool in = inside3(d, p[0], p[1], p[2], 0), deep = inside3(d, p[0], p[1], p[2], 2 * K + T3_X);
+  const long long o = u3idx(d, p[0], p[1], p[2]);
+  double hi[3], lo[3] = {0.0, 0.0, 0.0};
+  if (in) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) hi[c] = X.x[c][o];
+  } else {
+    const Pos3 r = c3_pos(d, p);
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
-      double s = 0.0;
-      for (int m = 1; m <= METRIC_REACH; ++m) {
-        const double cm = ms.d[m - 1];
-        if (cm == 0.0) continue;
-        int p1[3] = {p[0], p[1], p[2]}, p0[3] = {p[0], p[1], p[2]};
-        p1[a] += m;
-        p0[a] -= m;
-        s += cm * c3_diff(d, X.x[c], c, p1, p0);
+      double b, f;
+      c3_at(d, X.x[c], c, r, b, f);
+      two_sum(b, f, hi[c], lo[c]);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    xe[c * bx.pitch] = hi[c];
+    if (!deep) xe[(3 + c) * bx.pitch] = lo[c];
+  }
+}
+
+// Both derivative kernels work on tiles of 16 x 8 x 4 nodes, one per lane, and
+// take one outer direction o at a time: the tile and K nodes beyond both of
+// its faces across o (n_o + 2 K positions along o by the nodes across) are
+// staged in LDS, each value once where the lanes' taps read it 2 K times.
+// Sixteen nodes along i are one cache line of the aligned rows.
+// 150 x 131 x 117, WENOIU5-2MP: taps read from global memory (216 loads a node
+// in the nodal kernel, every one an L1 miss) took 550 + 210 us (nodal, inner),
+// tiles of 8 x 8 x 8 on unaligned rows 349 + 248 us.
+template <int O, int K> struct Stage3 {
+  static constexpr int A = (O == 0 ? T3_X : (O == 1 ? T3_Y : T3_Z)) + 2 * K;  // positions along o
+  static constexpr int C = O == 0 ? T3_Y * T3_Z : (O == 1 ? T3_X * T3_Z : T3_X * T3_Y);
+  // slots from one position along o to the next: the 32 lanes of an LDS
+  // access (sixteen along x by two along y) fall into different banks
+  static constexpr int S = O == 0 ? C + 2 : (O == 1 ? C + 16 : C);
+};
+template <int K> constexpr int stage3_slots() {
+  constexpr int a = Stage3<0, K>::A * Stage3<0, K>::S, b = Stage3<1, K>::A * Stage3<1, K>::S;
+  constexpr int c = Stage3<2, K>::A * Stage3<2, K>::S;
+  return a > b ? (a > c ? a : c) : (b > c ? b : c);
+}
+
+struct Tile3 {
+  int q[3];   // first node of the tile
+  int e[3];   // end of the box
+  int x, y, z;  // this lane's node in the tile
+  bool in;    // every position the tile reads is a node of the grid
+};
+
+WIU_DEV Tile3 tile3(const Dims3& d, const Box3& b, int K) {
+  const int n[3] = {T3_X, T3_Y, T3_Z};
+  Tile3 t;
+  int lid = xcd_remap(blockIdx.x, gridDim.x);
+  t.in = true;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int nt = (b.w[a] + n[a] - 1) / n[a];
+    t.q[a] = (lid % nt) * n[a] - b.h[a];
+    lid /= nt;
+    t.e[a] = d.n[a] + b.h[a];
+    t.in = t.in && t.q[a] >= K && t.q[a] + n[a] + K <= d.n[a];
+  }
+  t.x = threadIdx.x & 15; t.y = (threadIdx.x >> 4) & 7; t.z = threadIdx.x >> 7;
+  return t;
+}
+
+// Staged position e of direction O: its slot and node (positions beyond the
+// box's reach are clamped into it).
+template <int O, int K> WIU_DEV int tile3_pos(const Tile3& t, int e, int p[3]) {
+  using G = Stage3<O, K>;
+  const int cross = O == 0 ? e / G::A : e % G::C, a = O == 0 ? e % G::A : e / G::C;
+  p[0] = O == 0 ? a - K : cross & 15;
+  p[1] = O == 0 ? cross & 7 : (O == 1 ? a - K : cross >> 4);
+  p[2] = O == 0 ? cross >> 3 : (O == 1 ? cross >> 4 : a - K);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) p[q] = min(t.q[q] + p[q], t.e[q] - 1 + (q == O ? K : 0));
+  return a * G::S + cross;
+}
+
+// This lane's slot (its node) in direction O.
+template <int O, int K> WIU_DEV int tile3_slot(const Tile3& t) {
+  constexpr int S = Stage3<O, K>::S;
+  return O == 0 ? (t.x + K) * S + t.y + 8 * t.z : (O == 1 ? (t.y + K) * S + t.x + 16 * t.z : (t.z + K) * S + t.x + 16 * t.y);
+}
+
+// What a lane stages for one direction, held in registers between its loads
+// (all issued together, before the work on the direction before) and its
+// LDS stores: coordinates and, with G, three of the inner derivatives.  A
+// coordinate is the node coordinate itself in tiles that read nodes of the
+// grid only, else it is relative to the tile's first node.
+template <int O, int K, bool X, bool G> struct Lane3 {
+  static constexpr int N = (Stage3<O, K>::A * Stage3<O, K>::C + 511) / 512;
+  double x[N][3], g[N][3];
+  WIU_DEV void load(const Tile3& t, const Box3& bx, const double* __restrict__ XE, const Box3& bi,
+                    const double* __restrict__ Dx, int inner) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      int p[3];
+      tile3_pos<O, K>(t, min((int)threadIdx.x + 512 * n, Stage3<O, K>::A * Stage3<O, K>::C - 1), p);
+      if constexpr (X) {
+        const double* v = XE + b3idx(bx, 6, p[0], p[1], p[2]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x[n][c] = v[c * bx.pitch];
       }
-      Dx[(3 * a + c) * P + t] = s;
+      if constexpr (G) {
+        const double* v = Dx + b3idx(bi, 9, p[0], p[1], p[2]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) g[n][c] = v[(3 * inner + c) * bi.pitch];
+      }
+    }
+    if constexpr (X) {
+      if (!t.in) {
+        const double* v0 = XE + b3idx(bx, 6, t.q[0], t.q[1], t.q[2]);
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+          int p[3];
+          tile3_pos<O, K>(t, min((int)threadIdx.x + 512 * n, Stage3<O, K>::A * Stage3<O, K>::C - 1), p);
+          const double* v = XE + b3idx(bx, 6, p[0], p[1], p[2]);
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            x[n][c] = (x[n][c] - v0[c * bx.pitch]) + (v[(3 + c) * bx.pitch] - v0[(3 + c) * bx.pitch]);
+        }
+      }
+    }
+  }
+  WIU_DEV void store(const Tile3& t, double* L) const {
+    constexpr int NP = stage3_slots<K>();
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int e = threadIdx.x + 512 * n;
+      if (e >= Stage3<O, K>::A * Stage3<O, K>::C) break;
+      int p[3];
+      const int slot = tile3_pos<O, K>(t, e, p);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if constexpr (X) L[c * NP + slot] = x[n][c];
+        if constexpr (G) L[(3 + c) * NP + slot] = g[n][c];
+      }
+    }
+  }
+};
+
+// Derivatives along O of the three staged coordinates.
+template <int O, int K> WIU_DEV void inner3_dir(const Tile3& t, const MetricStencil& ms, const double* L, double s[3]) {
+  constexpr int NP = stage3_slots<K>(), S = Stage3<O, K>::S;
+  const double* v = L + tile3_slot<O, K>(t);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) s[c] = 0.0;
+#pragma unroll 1
+  for (int m = 1; m <= K; ++m)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s[c] += ms.d[m - 1] * (v[c * NP + m * S] - v[c * NP - m * S]);
+}
+
+// Inner derivatives D_a x_c (a, c = 0..2) on their box: component 3a + c.
+template <int K>
+__global__ void __launch_bounds__(512) m3_inner_kernel(Dims3 d, MetricStencil ms, Box3 bi, Box3 bx,
+                                                       const double* __restrict__ XE, double* __restrict__ Dx) {
+  __shared__ double L[3 * stage3_slots<K>()];
+  const Tile3 t = tile3(d, bi, K);
+  double s[9];
+  Lane3<0, K, true, false> l0;
+  Lane3<1, K, true, false> l1;
+  Lane3<2, K, true, false> l2;
+  l0.load(t, bx, XE, bi, Dx, 0);
+  l0.store(t, L);
+  __syncthreads();
+  l1.load(t, bx, XE, bi, Dx, 0);
+  inner3_dir<0, K>(t, ms, L, s);
+  __syncthreads();
+  l1.store(t, L);
+  __syncthreads();
+  l2.load(t, bx, XE, bi, Dx, 0);
+  inner3_dir<1, K>(t, ms, L, s + 3);
+  __syncthreads();
+  l2.store(t, L);
+  __syncthreads();
+  inner3_dir<2, K>(t, ms, L, s + 6);
+  const int i = t.q[0] + t.x, j = t.q[1] + t.y, k = t.q[2] + t.z;
+  if (i >= t.e[0] || j >= t.e[1] || k >= t.e[2]) return;
+  double* g = Dx + b3idx(bi, 9, i, j, k);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) g[q * bi.pitch] = s[q];
+}
+
+// Outer direction O of the nodal metrics: D_O(r x g_i) of the staged inner
+// direction i, added to n^_{O+2} (i = O+1) or taken from n^_{O+1} (i = O+2).
+template <int O, int K, int H>
+WIU_DEV void nodal3_dir(const Tile3& t, const MetricStencil& ms, const double* L, double nh[9]) {
+  constexpr int NP = stage3_slots<K>(), S = Stage3<O, K>::S, to = (O + 2 - H) % 3;
+  const double* v = L + tile3_slot<O, K>(t);
+  const double x0[3] = {v[0], v[NP], v[2 * NP]};
+#pragma unroll 1
+  for (int m = 1; m <= K; ++m)
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd) {
+      const double w = (sd != H) ? -ms.d[m - 1] : ms.d[m - 1];
+      const double* u = v + (sd ? -m : m) * S;
+      double r[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) r[c] = w * (u[c * NP] - x0[c]);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        const int p = (l + 1) % 3, q = (l + 2) % 3;
+        nh[3 * to + l] = fma(r[p], u[(3 + q) * NP], nh[3 * to + l]);
+        nh[3 * to + l] = fma(-r[q], u[(3 + p) * NP], nh[3 * to + l]);
+      }
     }
 }
 
-// Nodal metrics (Eq. 2.4) and J^{-1} (Eq. 2.5) on [-B, n+B)^3 into T[10]:
-// for direction m with (a, b) the next two directions cyclically and
-// component l with (p, q) the next two coordinates cyclically,
-//   n^_{m,l} = 1/2 [D_b(q D_a p) - D_a(q D_b p) + D_a(p D_b q) - D_b(p D_a q)],
-// with p, q taken relative to the node.  Periodic directions evaluate at the
-// wrapped node.
-__global__ void m3_nodal_kernel(Dims3 d, MetricStencil ms, int B, int E, Coord3 X, const double* __restrict__ Dx,
-                                double* __restrict__ T) {
-  const long long V0 = d.n[0] + 2 * B, V1 = d.n[1] + 2 * B, V2 = d.n[2] + 2 * B;
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long P = V0 * V1 * V2;
-  if (t >= P) return;
-  int w[3] = {(int)(t % V0) - B, (int)((t / V0) % V1) - B, (int)(t / (V0 * V1)) - B};
-  for (int a = 0; a < 3; ++a)
-    if (d.bc[a] == WIU_BC_PERIODIC) w[a] = bc_index(w[a], d.n[a], 0);
-  const long long W0 = d.n[0] + 2 * E, W1 = d.n[1] + 2 * E;
-  const long long DP = W0 * W1 * (d.n[2] + 2 * E);
-  auto dx = [&](int plane, const int p[3]) {
-    return Dx[plane * DP + ((long long)(p[2] + E) * W1 + (p[1] + E)) * W0 + (p[0] + E)];
-  };
+// Nodal metrics (Eq. 2.4) and J^{-1} (Eq. 2.5) on their box, ten components.
+// With r = x - x(node) and g_i = D_i x, Eq. 2.4 is for direction m and the next
+// two directions a, b cyclically
+//   n^_m = 1/2 [D_a(r x g_b) - D_b(r x g_a)].
+template <int K>
+__global__ void __launch_bounds__(512) m3_nodal_kernel(Dims3 d, MetricStencil ms, Box3 bt, Box3 bi, Box3 bx,
+                                                       const double* __restrict__ XE, const double* __restrict__ Dx,
+                                                       double* __restrict__ T) {
+  __shared__ double L[6 * stage3_slots<K>()];
+  const Tile3 t = tile3(d, bt, K);
+  double nh[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) nh[q] = 0.0;
+  // per outer direction the coordinates and g_{O+1}, then g_{O+2} in the
+  // place of g_{O+1}
+  Lane3<0, K, true, true> a0;
+  Lane3<0, K, false, true> b0;
+  Lane3<1, K, true, true> a1;
+  Lane3<1, K, false, true> b1;
+  Lane3<2, K, true, true> a2;
+  Lane3<2, K, false, true> b2;
+  a0.load(t, bx, XE, bi, Dx, 1);
+  a0.store(t, L);
+  __syncthreads();
+  b0.load(t, bx, XE, bi, Dx, 2);
+  nodal3_dir<0, K, 0>(t, ms, L, nh);
+  __syncthreads();
+  b0.store(t, L);
+  __syncthreads();
+  a1.load(t, bx, XE, bi, Dx, 2);
+  nodal3_dir<0, K, 1>(t, ms, L, nh);
+  __syncthreads();
+  a1.store(t, L);
+  __syncthreads();
+  b1.load(t, bx, XE, bi, Dx, 0);
+  nodal3_dir<1, K, 0>(t, ms, L, nh);
+  __syncthreads();
+  b1.store(t, L);
+  __syncthreads();
+  a2.load(t, bx, XE, bi, Dx, 0);
+  nodal3_dir<1, K, 1>(t, ms, L, nh);
+  __syncthreads();
+  a2.store(t, L);
+  __syncthreads();
+  b2.load(t, bx, XE, bi, Dx, 1);
+  nodal3_dir<2, K, 0>(t, ms, L, nh);
+  __syncthreads();
+  b2.store(t, L);
+  __syncthreads();
+  nodal3_dir<2, K, 1>(t, ms, L, nh);
+  const int i = t.q[0] + t.x, j = t.q[1] + t.y, k = t.q[2] + t.z;
+  if (i >= t.e[0] || j >= t.e[1] || k >= t.e[2]) return;
+  const double* g = Dx + b3idx(bi, 9, i, j, k);
+  double* tv = T + b3idx(bt, 10, i, j, k);
   double J = 0.0;
-  for (int m = 0; m < 3; ++m) {
-    const int a = (m + 1) % 3, b = (m + 2) % 3;
-    for (int l = 0; l < 3; ++l) {
-      const int pc = (l + 1) % 3, qc = (l + 2) % 3;
-      // D_outer((X_cv - X_cv(w)) D_inner X_cd)
-      auto term = [&](int outer, int cv, int inner, int cd) {
-        double s = 0.0;
-        for (int k = 1; k <= METRIC_REACH; ++k) {
-          const double ck = ms.d[k - 1];
-          if (ck == 0.0) continue;
-          int p1[3] = {w[0], w[1], w[2]}, p0[3] = {w[0], w[1], w[2]};
-          p1[outer] += k;
-          p0[outer] -= k;
-          const double f1 = c3_diff(d, X.x[cv], cv, p1, w) * dx(3 * inner + cd, p1);
-          const double f0 = c3_diff(d, X.x[cv], cv, p0, w) * dx(3 * inner + cd, p0);
-          s += ck * (f1 - f0);
-        }
-        return s;
-      };
-      const double v = 0.5 * (term(b, qc, a, pc) - term(a, qc, b, pc) + term(a, pc, b, qc) - term(b, pc, a, qc));
-      T[(3 * m + l) * P + t] = v;
-      J += v * dx(3 * m + l, w);
-    }
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    nh[q] *= 0.5;
+    J += nh[q] * g[q * bi.pitch];
+    tv[q * bt.pitch] = nh[q];
   }
-  T[9 * P + t] = J * (1.0 / 3.0);
+  tv[9 * bt.pitch] = J * (1.0 / 3.0);
 }
 
 // Stored metrics: nodal planes and midpoint interpolation in each metric's
 // own direction, ghost band included, plus the tag.  jform 6 replaces
 // J^{-1} by Eq. 2.6, 1/3 sum_{m,l} D_m(n^_{m,l} x_l) with x_l relative to
 // the (wrapped) node, which needs the nodal band B >= GHOST + METRIC_REACH.
-__global__ void m3_band_kernel(Dims3 d, int scheme, int B, const double* __restrict__ T, double* __restrict__ M,
-                               int* __restrict__ status, int jform, MetricStencil ms, Coord3 X, double ah) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) {
+template <bool J6>
+__global__ void __launch_bounds__(256) m3_band_kernel(Dims3 d, int scheme, Box3 bt, const double* __restrict__ T,
+                                                      double* __restrict__ M, int* __restrict__ status,
+                                                      MetricStencil ms, Coord3 X, double ah) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     double* tag = M + NP3 * d.mplane;
     tag[0] = TAG_MAGIC3; tag[1] = (double)scheme; tag[2] = (double)d.n[0]; tag[3] = (double)d.n[1];
     tag[4] = (double)d.n[2]; tag[5] = (double)(d.bc[0] + 2 * d.bc[1] + 4 * d.bc[2]); tag[6] = ah;
-    tag[7] = (double)jform;
+    tag[7] = J6 ? 6.0 : 5.0;
   }
-  if (t >= d.mplane) return;
-  const int p[3] = {(int)(t % d.mp[0]) - GHOST, (int)((t / d.mp[0]) % d.mp[1]) - GHOST,
-                    (int)(t / ((long long)d.mp[0] * d.mp[1])) - GHOST};
-  const long long V0 = d.n[0] + 2 * B, V1 = d.n[1] + 2 * B;
-  const long long TP = V0 * V1 * (d.n[2] + 2 * B);
-  auto tv = [&](int plane, int i, int j, int k) {
-    return T[plane * TP + ((long long)(k + B) * V1 + (j + B)) * V0 + (i + B)];
+  Box3 bm;
+  for (int a = 0; a < 3; ++a) { bm.h[a] = GHOST; bm.w[a] = d.n[a] + 2 * GHOST; }
+  int p[3];
+  if (!b3_node(bm, p[0], p[1], p[2])) return;
+  const long long t = m3idx(d, p[0], p[1], p[2]);
+  // offset of position q along direction a in the nodal box
+  const int W = bt.pitch;
+  long long st[3];
+  b3strides(bt, 10, st);
+  auto at = [&](int a, int q) {
+    return st[a] * (d.bc[a] == WIU_BC_PERIODIC ? bc_index(q, d.n[a], 0) : q + (a == 0 ? bt.off : bt.h[a]));
   };
-  for (int q = 0; q < 10; ++q) M[q * d.mplane + t] = tv(q, p[0], p[1], p[2]);
-  if (jform == 6) {
+  const long long o3[3] = {at(0, p[0]), at(1, p[1]), at(2, p[2])};
+  const double* v0 = T + (o3[0] + o3[1] + o3[2]);
+#pragma unroll
+  for (int q = 0; q < 10; ++q) M[q * d.mplane + t] = v0[q * W];
+  if constexpr (J6) {
     int w[3] = {p[0], p[1], p[2]};
     for (int a = 0; a < 3; ++a)
       if (d.bc[a] == WIU_BC_PERIODIC) w[a] = bc_index(w[a], d.n[a], 0);
@@ -201,27 +502,29 @@ __global__ void m3_band_kernel(Dims3 d, int scheme, int B, const double* __restr
           int p1[3] = {w[0], w[1], w[2]}, p0[3] = {w[0], w[1], w[2]};
           p1[m] += k;
           p0[m] -= k;
-          J += ck * (tv(3 * m + l, p1[0], p1[1], p1[2]) * c3_diff(d, X.x[l], l, p1, w) -
-                     tv(3 * m + l, p0[0], p0[1], p0[2]) * c3_diff(d, X.x[l], l, p0, w));
+          const double* v = v0 + ((3 * m + l) * W - o3[m]);
+          J += ck * (v[at(m, p1[m])] * c3_diff(d, X.x[l], l, p1, w) - v[at(m, p0[m])] * c3_diff(d, X.x[l], l, p0, w));
         }
     M[9 * d.mplane + t] = J * (1.0 / 3.0);
   }
   const bool eight = scheme >= 4;
-  for (int m = 0; m < 3; ++m)
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    long long q[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) q[s] = at(m, p[m] + (eight || (s > 0 && s < 7) ? s - 3 : 0)) - o3[m];
+#pragma unroll
     for (int l = 0; l < 3; ++l) {
-      auto v = [&](int s) {
-        int r[3] = {p[0], p[1], p[2]};
-        r[m] += s;
-        return tv(3 * m + l, r[0], r[1], r[2]);
-      };
+      const double* v = v0 + (3 * m + l) * W;
       M[(10 + 3 * m + l) * d.mplane + t] =
-          eight ? (-5.0 * (v(-3) + v(4)) + 49.0 * (v(-2) + v(3)) - 245.0 * (v(-1) + v(2)) +
-                   1225.0 * (v(0) + v(1))) * (1.0 / 2048.0)
-                : (3.0 * v(-2) - 25.0 * v(-1) + 150.0 * v(0) + 150.0 * v(1) - 25.0 * v(2) + 3.0 * v(3)) *
-                      (1.0 / 256.0);
+          eight ? (-5.0 * (v[q[0]] + v[q[7]]) + 49.0 * (v[q[1]] + v[q[6]]) - 245.0 * (v[q[2]] + v[q[5]]) +
+                   1225.0 * (v[q[3]] + v[q[4]])) * (1.0 / 2048.0)
+                : (3.0 * v[q[1]] - 25.0 * v[q[2]] + 150.0 * v[q[3]] + 150.0 * v[q[4]] - 25.0 * v[q[5]] +
+                   3.0 * v[q[6]]) * (1.0 / 256.0);
     }
-  if (p[0] >= 0 && p[0] < d.n[0] && p[1] >= 0 && p[1] < d.n[1] && p[2] >= 0 && p[2] < d.n[2]) {
-    const double j = M[9 * d.mplane + t];
+  }
+  if (inside3(d, p[0], p[1], p[2], 0)) {
+    const double j = J6 ? M[9 * d.mplane + t] : v0[9 * W];
     if (!(j > 0.0) || !(j < 1.0e300)) atomicOr(status, ST_JACOBIAN);
   }
 }
@@ -949,9 +1252,28 @@ Dims3 dims3(const wiu_grid3* g) {
 // stage) | dt | big area], the big area holding either the metric scratch
 // (inner derivatives, nodal band) or the stepping buffers (Racc, U1, U2).
 struct Ws3 {
-  size_t lam, lam2, dt, big, metric_dx, metric_t, racc, u1, u2, total;
+  size_t lam, lam2, dt, big, metric_dx, metric_t, metric_x, racc, u1, u2, total;
   long long nlam;
 };
+
+// A metric box: `band` beyond the grid along bounded directions, plus
+// `reach` along every direction.
+Box3 box3(const Dims3& d, int band, int reach) {
+  Box3 b;
+  for (int a = 0; a < 3; ++a) {
+    b.h[a] = (d.bc[a] == WIU_BC_PERIODIC ? 0 : band) + reach;
+    b.w[a] = d.n[a] + 2 * b.h[a];
+  }
+  b.off = (b.h[0] + 15) / 16 * 16;
+  b.pitch = (b.off + d.n[0] + b.h[0] + 15) / 16 * 16;
+  b.P = (long long)b.pitch * b.w[1] * b.w[2];
+  return b;
+}
+
+// The extended coordinates (six planes) stay in the metric array M, which
+// only the last metric kernel writes, unless the grid is so small that their
+// halo exceeds it.
+bool ext_in_metrics(const Dims3& d, const Box3& bx) { return 6 * bx.P <= NP3 * d.mplane; }
 
 Ws3 ws3(const wiu_grid3* g) {
   const Dims3 d = dims3(g);
@@ -964,16 +1286,16 @@ Ws3 ws3(const wiu_grid3* g) {
   w.lam2 = w.lam + set;  // the next RK stage's maxima
   w.dt = w.lam2 + set;
   w.big = w.dt + A3;
-  const int B = GHOST + METRIC_REACH, E = B + 8;  // the widest band (Eq. 2.6)
-  const size_t dxb = al3(9 * (size_t)(g->nx + 2 * E) * (g->ny + 2 * E) * (g->nz + 2 * E) * 8);
-  const size_t tb = al3(10 * (size_t)(g->nx + 2 * B) * (g->ny + 2 * B) * (g->nz + 2 * B) * 8);
+  const int B = GHOST + METRIC_REACH;  // the widest band (Eq. 2.6) and operator
+  const Box3 bx = box3(d, B, 2 * METRIC_REACH);
   w.metric_dx = w.big;
-  w.metric_t = w.big + dxb;
+  w.metric_t = w.metric_dx + al3(9 * (size_t)box3(d, B, METRIC_REACH).P * 8);
+  w.metric_x = w.metric_t + al3(10 * (size_t)box3(d, B, 0).P * 8);
   w.racc = w.big;
   w.u1 = w.racc + al3(5 * (size_t)d.np * 8);
   w.u2 = w.u1 + al3(5 * (size_t)d.np * 8);
   const size_t step_end = w.u2 + al3(5 * (size_t)d.np * 8);
-  const size_t met_end = w.metric_t + tb;
+  const size_t met_end = w.metric_x + (ext_in_metrics(d, bx) ? 0 : al3(6 * (size_t)bx.P * 8));
   w.total = step_end > met_end ? step_end : met_end;
   return w;
 }
@@ -1000,7 +1322,10 @@ void sides3(const wiu_grid3* g, S3Args& a) {
   }
 }
 
-dim3 lin_grid(long long n) { return dim3((unsigned)((n + 255) / 256)); }
+dim3 tile_grid(const Box3& b) {
+  return dim3((unsigned)((b.w[0] + T3_X - 1) / T3_X) * ((b.w[1] + T3_Y - 1) / T3_Y) * ((b.w[2] + T3_Z - 1) / T3_Z));
+}
+dim3 box_grid(const Box3& b) { return dim3((unsigned)(((b.w[0] * b.w[1] + 255) / 256) * b.w[2])); }
 
 // Tile shapes: xi 64 items x 4 lines (lanes along the line, one line per
 // wave), eta and zeta 32 items x 8 lines (lanes across the lines, along i).
@@ -1140,13 +1465,26 @@ int wiu3_metrics(const wiu_grid3* g, int scheme, int jform, const wiu_params* p,
   double* T = (double*)(base + w.metric_t);
   int* status = (int*)base;
   const MetricStencil ms = metric_stencil(scheme, ah);
-  const int B = jform == 6 ? GHOST + METRIC_REACH : metric_band(scheme), E = B + 8;
-  Coord3 X{{x, y, z}};
-  const long long ND = (long long)(d.n[0] + 2 * E) * (d.n[1] + 2 * E) * (d.n[2] + 2 * E);
-  const long long NT = (long long)(d.n[0] + 2 * B) * (d.n[1] + 2 * B) * (d.n[2] + 2 * B);
-  hipLaunchKernelGGL(m3_inner_kernel, lin_grid(ND), dim3(256), 0, st, d, ms, E, X, Dx);
-  hipLaunchKernelGGL(m3_nodal_kernel, lin_grid(NT), dim3(256), 0, st, d, ms, B, E, X, Dx, T);
-  hipLaunchKernelGGL(m3_band_kernel, lin_grid(d.mplane), dim3(256), 0, st, d, scheme, B, T, M, status, jform, ms, X, ah);
+  int K = METRIC_REACH;
+  while (K > 3 && ms.d[K - 1] == 0.0) --K;
+  const int B = jform == 6 ? GHOST + METRIC_REACH : metric_band(scheme);
+  const Box3 bt = box3(d, B, 0), bi = box3(d, B, K), bx = box3(d, B, 2 * K);
+  double* XE = ext_in_metrics(d, bx) ? M : (double*)(base + w.metric_x);
+  const Coord3 X{{x, y, z}};
+  Box3 bm;
+  for (int q = 0; q < 3; ++q) bm.w[q] = d.n[q] + 2 * GHOST;
+  hipLaunchKernelGGL(m3_ext_kernel, box_grid(bx), dim3(256), 0, st, d, bx, K, X, XE);
+#define WIU_M3(k)                                                                                      \
+  case k:                                                                                              \
+    hipLaunchKernelGGL(m3_inner_kernel<k>, tile_grid(bi), dim3(512), 0, st, d, ms, bi, bx, XE, Dx);    \
+    hipLaunchKernelGGL(m3_nodal_kernel<k>, tile_grid(bt), dim3(512), 0, st, d, ms, bt, bi, bx, XE, Dx, T); \
+    break;
+  switch (K) { WIU_M3(3) WIU_M3(4) WIU_M3(5) WIU_M3(6) WIU_M3(7) }
+#undef WIU_M3
+  if (jform == 6)
+    hipLaunchKernelGGL(m3_band_kernel<true>, box_grid(bm), dim3(256), 0, st, d, scheme, bt, T, M, status, ms, X, ah);
+  else
+    hipLaunchKernelGGL(m3_band_kernel<false>, box_grid(bm), dim3(256), 0, st, d, scheme, bt, T, M, status, ms, X, ah);
   return rc3(hipGetLastError());
 }
 

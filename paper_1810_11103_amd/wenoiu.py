@@ -624,8 +624,11 @@ class Solver3:
         nw = lib.wiu3_workspace_bytes(ctypes.byref(self.grid))
         if nm == 0 or nw == 0:
             raise WiuError("invalid 3-D grid")
-        self.M = torch.zeros(nm // 8, dtype=torch.float64, device=device)
-        self.ws = torch.zeros(nw, dtype=torch.uint8, device=device)
+        # the metric kernels write all of M, and every call writes its part of
+        # the workspace before reading it; only the status word starts at zero
+        self.M = torch.empty(nm // 8, dtype=torch.float64, device=device)
+        self.ws = torch.empty(nw, dtype=torch.uint8, device=device)
+        workspace_init(self.ws)
         self.dt = torch.zeros(1, dtype=torch.float64, device=device)
         xyz = [torch.as_tensor(a, dtype=torch.float64).to(device).contiguous() for a in (x, y, z)]
         _check(lib.wiu3_metrics(ctypes.byref(self.grid), scheme_id(scheme), int(jform), ctypes.byref(self.params),
