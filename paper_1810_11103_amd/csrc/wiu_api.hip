@@ -67,13 +67,14 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 //   0            header: int status, padding
 //   HDR          lam_xi[ny], lam_eta[nx], cfl_max[1], cfl per eta line[nx]
 //                (uint64 bit patterns)
-//   lam2         a second such set (maxima of an RK stage state)
+//   lam2, lam3   two more such sets (maxima of RK stage states; the sets are
+//                contiguous, lam3 is used by the stage tiles only)
 //   off_scratch  R^xi[4 np], U1[4 np], U2[4 np]  -- or the metric band temp
 //   then the adjoint region: Ubar2, Ubar1 (4 planes each), eigenvalue
 //   partials [max lines x segments] (double) and first maximal nodes (int),
 //   off-line contributions [max lines][2][6][4]
 struct WsLayout {
-  size_t lam, lam2, scratch, rxi, u1, u2, ub2, ub1, lpx, lpe, apx, ape, ghx, ghe, total;
+  size_t lam, lam2, lam3, scratch, rxi, u1, u2, ub2, ub1, lpx, lpe, apx, ape, ghx, ghe, total;
 };
 
 WsLayout layout(const wiu_grid* g) {
@@ -87,7 +88,8 @@ WsLayout layout(const wiu_grid* g) {
   const size_t set = align_up(((size_t)2 * g->nx + g->ny + 1) * 8);
   L.lam = ALIGN;
   L.lam2 = L.lam + set;
-  L.scratch = L.lam2 + set;
+  L.lam3 = L.lam2 + set;
+  L.scratch = L.lam3 + set;
   L.rxi = L.scratch;
   L.u1 = L.rxi + plane4;
   L.u2 = L.u1 + plane4;
@@ -175,6 +177,7 @@ struct Ws {
   int* status;
   unsigned long long *lx, *le, *cfl;
   unsigned long long *lx2, *le2;  // maxima of an RK stage state, from the previous stage
+  unsigned long long* lx3;        // a third set (stage tiles), the same distance further
   double *rxi, *u1, *u2, *band;
   double *ub2, *ub1, *lpx, *lpe, *ghx, *ghe;  // adjoint: per direction, eigenvalue partials and ghosts
   int *apx, *ape;                            //   and first maximal nodes
@@ -190,6 +193,7 @@ Ws carve(const wiu_grid* g, void* ws) {
   w.cfl = w.le + g->nx;
   w.lx2 = (unsigned long long*)(b + L.lam2);
   w.le2 = w.lx2 + g->ny;
+  w.lx3 = (unsigned long long*)(b + L.lam3);
   w.rxi = (double*)(b + L.rxi);
   w.u1 = (double*)(b + L.u1);
   w.u2 = (double*)(b + L.u2);
@@ -244,9 +248,9 @@ int residual_vjp(const wiu_grid* g, int scheme, const wiu_params* p, const doubl
 
 int hip_rc(hipError_t e) { return e == hipSuccess ? WIU_OK : WIU_EHIP; }
 
-// Residual pieces shared by rhs and the RK stages: line maxima, then the xi
-// sweep into R^xi, then the eta sweep with the requested epilogue.  The
-// maxima are computed here unless given (lx_in/le_in, accumulated by the
+// Residual pieces shared by rhs and the RK stages: line maxima, then on small
+// grids one launch of stage tiles (wiu_stage.hpp), on others the xi sweep into
+// R^xi and the eta sweep with the requested epilogue.  The maxima are computed here unless given (lx_in/le_in, accumulated by the
 // previous stage); with nlx/nle (mode 2 only) the eta sweep accumulates the
 // maxima of the new stage state there.
 struct Maxima {
@@ -254,7 +258,21 @@ struct Maxima {
   unsigned long long *nlx = nullptr, *nle = nullptr;
   unsigned long long* ncfl = nullptr;  // with nlx: per eta line CFL maxima of the new state (nlx + nx + ny + 1)
   unsigned long long* wm = nullptr;  // target of the separate pass (lx[ny], le[nx], cfl[1]); default the workspace's
+  bool cleared = false;              // nlx (and ncfl) are zero already
+  // stage tiles only (StageArgs): the step size from CFL maxima, a set to
+  // clear for the stage after next, a copy of the source state
+  const unsigned long long* cflw = nullptr;
+  int ncflw = 0;
+  double cfl = 0.0;
+  double* dt_out = nullptr;
+  unsigned long long* clear = nullptr;
+  double* copy = nullptr;
 };
+
+bool stage_tiles(const wiu_grid* g) { return use_stage_tiles((long long)g->nx * g->ny); }
+
+// Words of a maxima set with its per-line CFL maxima.
+long long set_words(const wiu_grid* g) { return 2LL * g->nx + g->ny + 1; }
 
 int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U, const double* M, const Ws& w,
              int mode, double* out, const double* U0, const double* dt, double ca, double cb, hipStream_t st,
@@ -278,6 +296,22 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
     a.side[k] = periodic ? WIU_SIDE_TRANSMISSIVE : g->side[k];
     for (int c = 0; c < 4; ++c) a.fixed[k][c] = g->fixed[k][c];
   }
+  const bool next = mode == 2 && mx.nlx;
+  // one set is contiguous: lam_xi[ny], lam_eta[nx], cfl[1] (and the per-line
+  // CFL maxima[nx] when they are accumulated too)
+  const long long next_len = (long long)d.nx + d.ny + 1 + (mx.ncfl ? d.nx : 0);
+  if (stage_tiles(g)) {
+    StageArgs t;
+    t.s = a;
+    t.s.mode = mode; t.s.Rxi = nullptr; t.s.out = out; t.s.U0 = U0; t.s.dt = dt; t.s.ca = ca; t.s.cb = cb;
+    t.s.status = w.status;
+    t.s.nlam_xi = next ? mx.nlx : nullptr; t.s.nlam_eta = next ? mx.nle : nullptr; t.s.ncfl = next ? mx.ncfl : nullptr;
+    t.cflw = mx.cflw; t.ncflw = mx.ncflw; t.cfl = mx.cfl; t.dt_out = mx.dt_out;
+    t.clear = mx.clear; t.nclear = set_words(g); t.copy = mx.copy;
+    if (next && !mx.cleared && launch_fill_u64(mx.nlx, next_len, st) != hipSuccess) return WIU_EHIP;
+    ProfScope ps(WIU_K_SWEEP_ETA, st);
+    return hip_rc(launch_stage(scheme, t, st));
+  }
   a.mode = mode == 2 ? 3 : 0; a.Rxi = w.rxi; a.out = out; a.U0 = U0; a.dt = dt; a.ca = ca; a.cb = cb;
   a.status = w.status;
   a.nlam_xi = nullptr; a.nlam_eta = nullptr; a.ncfl = nullptr;
@@ -287,11 +321,8 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
   }
   if (e != hipSuccess) return WIU_EHIP;
   a.mode = mode;
-  if (mode == 2 && mx.nlx) {
-    // one set is contiguous: lam_xi[ny], lam_eta[nx], cfl[1] (and the per-line
-    // CFL maxima[nx] when they are accumulated too)
-    const long long len = (long long)d.nx + d.ny + 1 + (mx.ncfl ? d.nx : 0);
-    if (launch_fill_u64(mx.nlx, len, st) != hipSuccess) return WIU_EHIP;
+  if (next) {
+    if (!mx.cleared && launch_fill_u64(mx.nlx, next_len, st) != hipSuccess) return WIU_EHIP;
     a.nlam_xi = mx.nlx; a.nlam_eta = mx.nle; a.ncfl = mx.ncfl;
   }
   {
@@ -303,9 +334,8 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
 
 // The three Shu-Osher TVD-RK3 stages (Sec. 4.2):
 //   U1 = U + dt L(U); U2 = 3/4 U + 1/4 (U1 + dt L(U1)); U <- 1/3 U + 2/3 (U2 + dt L(U2)).
-// The first stage's line maxima are computed from U (or taken from a
-// preceding CFL evaluation of the same state, have_max); stages 1 and 2
-// accumulate the maxima of U1 and U2 in their eta sweeps.
+// The first stage's line maxima are computed from U; stages 1 and 2
+// accumulate the maxima of U1 and U2 as they write them.
 // rec (optional, a step record): the three maxima sets go there instead of
 // the workspace, U's at rec[0], U1's at rec[1], U2's at rec[2].
 //
@@ -313,23 +343,34 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
 // the partial update P only at its own output node, so it may write the new
 // stage state over P: stage 1 puts P and then U1 in U1's buffer, stage 2 P
 // and U2 in U2's, and stage 3 its P in U1's buffer (U1 is no longer read).
-int rk3_stages(const wiu_grid* g, int scheme, const wiu_params* p, double* U, const double* M, const double* dt,
-               double* U1, double* U2, const Ws& w, hipStream_t st, bool have_max,
-               unsigned long long* rec = nullptr, bool inplace = false) {
+// Stage tiles use three maxima sets, all cleared by one launch: U's, U1's and
+// U2's own (or the record's).  With cfl > 0 the first stage forms the step size
+// from U's CFL maximum and writes it to dt.
+int rk3_stages(const wiu_grid* g, int scheme, const wiu_params* p, double* U, const double* M, double* dt, double* U1,
+               double* U2, const Ws& w, hipStream_t st, double cfl = 0.0, unsigned long long* rec = nullptr,
+               bool inplace = false) {
   const long long ns = (long long)g->nx + g->ny + 1;
-  unsigned long long* m0 = rec ? rec : w.lx;              // maxima of U
-  unsigned long long* mA = rec ? rec + ns : w.lx2;        // of U1
-  unsigned long long* mB = rec ? rec + 2 * ns : w.lx;     // of U2
+  const bool tiles = stage_tiles(g);
+  unsigned long long* m0 = rec ? rec : w.lx;                             // maxima of U
+  unsigned long long* mA = rec ? rec + ns : w.lx2;                       // of U1
+  unsigned long long* mB = rec ? rec + 2 * ns : (tiles ? w.lx3 : w.lx);  // of U2
+  if (tiles && launch_fill_u64(m0, mB + ns - m0, st) != hipSuccess) return WIU_EHIP;
+  {
+    ProfScope ps(WIU_K_WAVE_MAX, st);
+    if (launch_wave_max(dims(g), U, M, p->gamma, m0, m0 + g->ny, m0 + ns - 1, w.status, st, tiles) != hipSuccess)
+      return WIU_EHIP;
+  }
   Ws w1 = w, w2 = w, w3 = w;
   if (inplace) { w1.rxi = U1; w2.rxi = U2; w3.rxi = U1; }
   Maxima m1;
-  if (have_max) { m1.lx_in = w.lx; m1.le_in = w.le; }
-  m1.wm = m0;
-  m1.nlx = mA; m1.nle = mA + g->ny;
+  m1.lx_in = m0; m1.le_in = m0 + g->ny;
+  m1.nlx = mA; m1.nle = mA + g->ny; m1.cleared = tiles;
+  if (cfl > 0.0 && tiles) { m1.cflw = m0 + ns - 1; m1.ncflw = 1; m1.cfl = cfl; m1.dt_out = dt; }
+  if (cfl > 0.0 && !tiles && launch_cfl_dt(m0 + ns - 1, cfl, dt, st) != hipSuccess) return WIU_EHIP;
   int rc = residual(g, scheme, p, U, M, w1, 2, U1, U, dt, 0.0, 1.0, st, m1);
   if (rc) return rc;
   Maxima m2;
-  m2.lx_in = mA; m2.le_in = mA + g->ny; m2.nlx = mB; m2.nle = mB + g->ny;
+  m2.lx_in = mA; m2.le_in = mA + g->ny; m2.nlx = mB; m2.nle = mB + g->ny; m2.cleared = tiles;
   rc = residual(g, scheme, p, U1, M, w2, 2, U2, U, dt, 0.75, 0.25, st, m2);
   if (rc) return rc;
   Maxima m3;
@@ -347,10 +388,10 @@ constexpr int NOALLOC_MAX_DEVICES = 64;
 std::mutex g_noalloc_mu;
 void* g_noalloc_ptr[NOALLOC_MAX_DEVICES] = {};
 
-// Layout in the scratch: two sets of line maxima, then the two stage
-// buffers (P / U1 and P / U2, see rk3_stages).
+// Layout in the scratch: two sets of line maxima (three with stage tiles),
+// then the two stage buffers (P / U1 and P / U2, see rk3_stages).
 struct NoallocLayout {
-  size_t lam, lam2, a, b, total;
+  size_t lam, lam2, lam3, a, b, total;  // lam3: stage tiles only (small grids, far below the limit)
 };
 NoallocLayout noalloc_layout(const wiu_grid* g) {
   NoallocLayout L;
@@ -358,7 +399,8 @@ NoallocLayout noalloc_layout(const wiu_grid* g) {
   const size_t lam = align_up(((size_t)g->nx + g->ny + 1) * 8);
   L.lam = 0;
   L.lam2 = lam;
-  L.a = 2 * lam;
+  L.lam3 = 2 * lam;
+  L.a = (stage_tiles(g) ? 3 : 2) * lam;
   L.b = L.a + align_up(4 * np * 8);
   L.total = L.b + align_up(4 * np * 8);
   return L;
@@ -451,7 +493,7 @@ int wiu_rk3_step(const wiu_grid* g, int scheme, const wiu_params* p, double* U, 
                  const double* dt_dev, void* ws, wiu_stream_t stream) {
   if (!grid_ok(g) || !options_ok(scheme, p) || !U || !M || !dt_dev || !ws) return WIU_EINVAL;
   Ws w = carve(g, ws);
-  return rk3_stages(g, scheme, p, U, M, dt_dev, w.u1, w.u2, w, (hipStream_t)stream, false);
+  return rk3_stages(g, scheme, p, U, M, const_cast<double*>(dt_dev), w.u1, w.u2, w, (hipStream_t)stream);
 }
 
 int wiu_rk3_step_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double* U, const double* M, double cfl,
@@ -459,13 +501,7 @@ int wiu_rk3_step_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double*
   if (!grid_ok(g) || !options_ok(scheme, p) || !U || !M || !dt_dev || !ws || !(cfl > 0.0))
     return WIU_EINVAL;
   Ws w = carve(g, ws);
-  hipStream_t st = (hipStream_t)stream;
-  {
-    ProfScope ps(WIU_K_WAVE_MAX, st);
-    if (launch_wave_max(dims(g), U, M, p->gamma, w.lx, w.le, w.cfl, w.status, st) != hipSuccess) return WIU_EHIP;
-  }
-  if (launch_cfl_dt(w.cfl, cfl, dt_dev, st) != hipSuccess) return WIU_EHIP;
-  return rk3_stages(g, scheme, p, U, M, dt_dev, w.u1, w.u2, w, st, true);
+  return rk3_stages(g, scheme, p, U, M, dt_dev, w.u1, w.u2, w, (hipStream_t)stream, cfl);
 }
 
 int wiu_rk3_steps_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double* U, const double* M, double cfl,
@@ -475,35 +511,46 @@ int wiu_rk3_steps_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double
   Ws w = carve(g, ws);
   hipStream_t st = (hipStream_t)stream;
   const long long ny = g->ny, nxy = (long long)g->nx + g->ny;
-  // two maxima sets (lam_xi[ny], lam_eta[nx], cfl[1], cfl per eta line[nx]):
-  // sa holds the current state's, sb receives the next stage's; they swap
-  // roles stage by stage.  The first step's come from the separate pass (one
-  // CFL maximum), later steps' from the step before (per-line CFL maxima).
+  // maxima sets (lam_xi[ny], lam_eta[nx], cfl[1], cfl per eta line[nx]): sa
+  // holds the current state's, sb receives the next stage's; they swap roles
+  // stage by stage.  The first step's come from the separate pass (one CFL
+  // maximum), later steps' from the step before (per-line CFL maxima).  Stage
+  // tiles rotate three sets: a stage clears the one its successor accumulates,
+  // whose last reader was its predecessor.
+  const bool tiles = stage_tiles(g);
   unsigned long long* sa = w.lx;
   unsigned long long* sb = w.lx2;
+  unsigned long long* sc = tiles ? w.lx3 : w.lx;
+  if (tiles && launch_fill_u64(sa, sb + set_words(g) - sa, st) != hipSuccess) return WIU_EHIP;
   {
     ProfScope ps(WIU_K_WAVE_MAX, st);
-    if (launch_wave_max(dims(g), U, M, p->gamma, sa, sa + ny, sa + nxy, w.status, st) != hipSuccess) return WIU_EHIP;
+    if (launch_wave_max(dims(g), U, M, p->gamma, sa, sa + ny, sa + nxy, w.status, st, tiles) != hipSuccess)
+      return WIU_EHIP;
   }
+  const double ca[3] = {0.0, 0.75, 1.0 / 3.0}, cb[3] = {1.0, 0.25, 2.0 / 3.0};
+  const double* src[3] = {U, w.u1, w.u2};
+  double* dst[3] = {w.u1, w.u2, U};
   for (int s = 0; s < nsteps; ++s) {
     double* dt = dt_dev + s;
-    if ((s == 0 ? launch_cfl_dt(sa + nxy, cfl, dt, st) : launch_cfl_dt_lines(sa + nxy + 1, g->nx, cfl, dt, st)) !=
-        hipSuccess)
+    const unsigned long long* cflw = s == 0 ? sa + nxy : sa + nxy + 1;
+    if (!tiles && (s == 0 ? launch_cfl_dt(cflw, cfl, dt, st) : launch_cfl_dt_lines(cflw, g->nx, cfl, dt, st)) != hipSuccess)
       return WIU_EHIP;
-    Maxima m1;  // U in, U1 out
-    m1.lx_in = sa; m1.le_in = sa + ny; m1.nlx = sb; m1.nle = sb + ny;
-    int rc = residual(g, scheme, p, U, M, w, 2, w.u1, U, dt, 0.0, 1.0, st, m1);
-    if (rc) return rc;
-    Maxima m2;  // U1 in, U2 out
-    m2.lx_in = sb; m2.le_in = sb + ny; m2.nlx = sa; m2.nle = sa + ny;
-    rc = residual(g, scheme, p, w.u1, M, w, 2, w.u2, U, dt, 0.75, 0.25, st, m2);
-    if (rc) return rc;
-    Maxima m3;  // U2 in; the new state's maxima and CFL maximum out, unless last
-    m3.lx_in = sa; m3.le_in = sa + ny;
-    if (s + 1 < nsteps) { m3.nlx = sb; m3.nle = sb + ny; m3.ncfl = sb + nxy + 1; }
-    rc = residual(g, scheme, p, w.u2, M, w, 2, U, U, dt, 1.0 / 3.0, 2.0 / 3.0, st, m3);
-    if (rc) return rc;
-    std::swap(sa, sb);
+    for (int q = 0; q < 3; ++q) {
+      Maxima m;  // of the source state in, of the new one out (unless last)
+      m.lx_in = sa; m.le_in = sa + ny;
+      if (q < 2 || s + 1 < nsteps) {
+        m.nlx = sb; m.nle = sb + ny;
+        if (q == 2) m.ncfl = sb + nxy + 1;
+        if (tiles) { m.cleared = true; m.clear = sc; }
+      }
+      if (tiles && q == 0) { m.cflw = cflw; m.ncflw = s == 0 ? 1 : g->nx; m.cfl = cfl; m.dt_out = dt; }
+      const int rc = residual(g, scheme, p, src[q], M, w, 2, dst[q], U, dt, ca[q], cb[q], st, m);
+      if (rc) return rc;
+      unsigned long long* last = sa;  // free now
+      sa = sb;
+      sb = tiles ? sc : last;
+      sc = last;
+    }
   }
   return WIU_OK;
 }
@@ -528,11 +575,12 @@ int wiu_rk3_step_noalloc(const wiu_grid* g, int scheme, const wiu_params* p, dou
   w.cfl = w.le + g->nx;
   w.lx2 = (unsigned long long*)(b + L.lam2);
   w.le2 = w.lx2 + g->ny;
+  w.lx3 = (unsigned long long*)(b + L.lam3);
   double* A = (double*)(b + L.a);
   double* B = (double*)(b + L.b);
-  // every maxima set is cleared by a fill kernel before it is accumulated,
-  // and both stage buffers are written before they are read
-  return rk3_stages(g, scheme, p, U, M, dt_dev, A, B, w, (hipStream_t)stream, false, nullptr, true);
+  // every maxima set is cleared before it is accumulated, and both stage
+  // buffers are written before they are read
+  return rk3_stages(g, scheme, p, U, M, const_cast<double*>(dt_dev), A, B, w, (hipStream_t)stream, 0.0, nullptr, true);
 }
 
 int wiu_rhs_vjp(const wiu_grid* g, int scheme, const wiu_params* p, const double* U, const double* M,
@@ -554,7 +602,8 @@ int wiu_rk3_step_stages(const wiu_grid* g, int scheme, const wiu_params* p, doub
   if (!grid_ok(g) || !options_ok(scheme, p) || !U || !M || !dt_dev || !U1 || !U2 || !ws)
     return WIU_EINVAL;
   Ws w = carve(g, ws);
-  return rk3_stages(g, scheme, p, U, M, dt_dev, U1, U2, w, (hipStream_t)stream, false, (unsigned long long*)rec);
+  return rk3_stages(g, scheme, p, U, M, const_cast<double*>(dt_dev), U1, U2, w, (hipStream_t)stream, 0.0,
+                    (unsigned long long*)rec);
 }
 
 int wiu_rk3_steps_stages(const wiu_grid* g, int scheme, const wiu_params* p, double* U, const double* M,
@@ -567,30 +616,33 @@ int wiu_rk3_steps_stages(const wiu_grid* g, int scheme, const wiu_params* p, dou
   const size_t plane4 = (size_t)4 * g->nx * g->ny;
   unsigned long long* r = (unsigned long long*)recs;
   // the first step's maxima of U from a separate pass, into its record;
-  // later steps' from the last stage of the step before
+  // later steps' from the last stage of the step before.  Stage tiles have all
+  // records cleared by one launch and copy U_n as they stage it.
+  const bool tiles = stage_tiles(g);
+  if (tiles && launch_fill_u64(r, 3 * ns * nsteps, st) != hipSuccess) return WIU_EHIP;
   {
     ProfScope ps(WIU_K_WAVE_MAX, st);
-    if (launch_wave_max(dims(g), U, M, p->gamma, r, r + ny, r + ns - 1, w.status, st) != hipSuccess) return WIU_EHIP;
+    if (launch_wave_max(dims(g), U, M, p->gamma, r, r + ny, r + ns - 1, w.status, st, tiles) != hipSuccess)
+      return WIU_EHIP;
   }
+  const double ca[3] = {0.0, 0.75, 1.0 / 3.0}, cb[3] = {1.0, 0.25, 2.0 / 3.0};
   for (int s = 0; s < nsteps; ++s) {
     double* S0 = stages + (size_t)s * 3 * plane4;
     double* S1 = S0 + plane4;
     double* S2 = S1 + plane4;
-    unsigned long long* rs = r + (long long)s * 3 * ns;
-    if (hipMemcpyAsync(S0, U, plane4 * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess) return WIU_EHIP;
-    Maxima m1;  // U in, U1 out
-    m1.lx_in = rs; m1.le_in = rs + ny; m1.nlx = rs + ns; m1.nle = rs + ns + ny;
-    int rc = residual(g, scheme, p, U, M, w, 2, S1, U, dt_dev, 0.0, 1.0, st, m1);
-    if (rc) return rc;
-    Maxima m2;  // U1 in, U2 out
-    m2.lx_in = rs + ns; m2.le_in = rs + ns + ny; m2.nlx = rs + 2 * ns; m2.nle = rs + 2 * ns + ny;
-    rc = residual(g, scheme, p, S1, M, w, 2, S2, U, dt_dev, 0.75, 0.25, st, m2);
-    if (rc) return rc;
-    Maxima m3;  // U2 in; the new state's maxima into the next step's record
-    m3.lx_in = rs + 2 * ns; m3.le_in = rs + 2 * ns + ny;
-    if (s + 1 < nsteps) { m3.nlx = rs + 3 * ns; m3.nle = rs + 3 * ns + ny; }
-    rc = residual(g, scheme, p, S2, M, w, 2, U, U, dt_dev, 1.0 / 3.0, 2.0 / 3.0, st, m3);
-    if (rc) return rc;
+    const double* src[3] = {U, S1, S2};
+    double* dst[3] = {S1, S2, U};
+    if (!tiles && hipMemcpyAsync(S0, U, plane4 * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
+      return WIU_EHIP;
+    for (int q = 0; q < 3; ++q) {
+      unsigned long long* rs = r + (3 * (long long)s + q) * ns;
+      Maxima m;  // of the source state in, of the new one into the record after (unless last)
+      m.lx_in = rs; m.le_in = rs + ny;
+      if (q < 2 || s + 1 < nsteps) { m.nlx = rs + ns; m.nle = rs + ns + ny; m.cleared = tiles; }
+      if (tiles && q == 0) m.copy = S0;
+      const int rc = residual(g, scheme, p, src[q], M, w, 2, dst[q], U, dt_dev, ca[q], cb[q], st, m);
+      if (rc) return rc;
+    }
   }
   return WIU_OK;
 }

@@ -423,6 +423,8 @@ WIU_DEV void mid_split_alt(int split, const double Q[4], double mx, double my, i
 //   side 1: F^-_{k+1/2}, reference Q_{k+1}, right-biased over k+3..k-1
 //   (nx_, ny_): unit normal of the averaged nodal metric; (mx, my): midpoint
 //   metric; lam: line eigenvalue.
+//   A caller that mirrors the stencil itself passes side 0 and, for F^-, -lam;
+//   sside then names the side for another midpoint split.
 // The projection acts on deviations from the reference state (exact for a
 // uniform state) with the left eigenvectors factored as
 //   l_1 = (A + B)/2, l_2 = e_rho - A, l_4 = (A - B)/2 applied to dQ, with
@@ -430,7 +432,7 @@ WIU_DEV void mid_split_alt(int split, const double Q[4], double mx, double my, i
 // ---------------------------------------------------------------------------
 template <bool FIFTH, bool ZOK = false, class QF>
 WIU_DEV void side_flux(QF q, int side, double nx_, double ny_, double mx, double my, double lam, double gam,
-                       double eps, int ppm, double F[4], int split = 0, double* Dacc = nullptr) {
+                       double eps, int ppm, double F[4], int split = 0, double* Dacc = nullptr, int sside = -1) {
   const double Qr[4] = {q(2 + side, 0), q(2 + side, 1), q(2 + side, 2), q(2 + side, 3)};
   const double gm1 = gam - 1.0;
   const double rr = rcp(Qr[0]);
@@ -489,7 +491,7 @@ WIU_DEV void side_flux(QF q, int side, double nx_, double ny_, double mx, double
     // another split for the leading midpoint flux: accumulate its difference
     const double Qm[4] = {r0, r1, r2, r3};
     double G[4];
-    mid_split_alt(split, Qm, mx, my, side, gam, G);
+    mid_split_alt(split, Qm, mx, my, sside < 0 ? side : sside, gam, G);
 #pragma unroll
     for (int c = 0; c < 4; ++c) Dacc[c] += G[c] - F[c];
   }
@@ -504,7 +506,7 @@ WIU_DEV void side_flux(QF q, int side, double nx_, double ny_, double mx, double
 // instead of twenty-four (compiler barriers keep the passes apart).
 template <bool ZOK = false, class QF>
 WIU_DEV void side_flux7(QF q, int side, double nx_, double ny_, double mx, double my, double lam, double gam,
-                        double eps, int ppm, double F[4], int split = 0, double* Dacc = nullptr) {
+                        double eps, int ppm, double F[4], int split = 0, double* Dacc = nullptr, int sside = -1) {
   const double Qr[4] = {q(3 + side, 0), q(3 + side, 1), q(3 + side, 2), q(3 + side, 3)};
   const double gm1 = gam - 1.0;
   const double rr = rcp(Qr[0]);
@@ -574,7 +576,7 @@ WIU_DEV void side_flux7(QF q, int side, double nx_, double ny_, double mx, doubl
     // another split for the leading midpoint flux: accumulate its difference
     const double Qm[4] = {r0, r1, r2, r3};
     double G[4];
-    mid_split_alt(split, Qm, mx, my, side, gam, G);
+    mid_split_alt(split, Qm, mx, my, sside < 0 ? side : sside, gam, G);
 #pragma unroll
     for (int c = 0; c < 4; ++c) Dacc[c] += G[c] - F[c];
   }
@@ -590,7 +592,7 @@ WIU_DEV void side_flux7(QF q, int side, double nx_, double ny_, double mx, doubl
 // with one reciprocal density per stencil point.
 template <int R, bool ZOK = false, class QF>
 WIU_DEV void side_flux_comp(QF q, int side, int vars, double mx, double my, double lam, double gam, double eps,
-                            int ppm, double F[4], int split = 0, double* Dacc = nullptr) {
+                            int ppm, double F[4], int split = 0, double* Dacc = nullptr, int sside = -1) {
   constexpr int QL = R == 4 ? 3 : 2;        // reference position in the window (side 0)
   constexpr int NS = R == 2 ? 4 : 2 * R - 1;  // stencil positions s = 0..NS-1, reference at s = QL
   const double gm1 = gam - 1.0;
@@ -641,7 +643,7 @@ WIU_DEV void side_flux_comp(QF q, int side, int vars, double mx, double my, doub
     // another split for the leading midpoint flux: accumulate its difference
     const double Qm[4] = {r0, r1, r2, r3};
     double G[4];
-    mid_split_alt(split, Qm, mx, my, side, gam, G);
+    mid_split_alt(split, Qm, mx, my, sside < 0 ? side : sside, gam, G);
 #pragma unroll
     for (int c = 0; c < 4; ++c) Dacc[c] += G[c] - F[c];
   }

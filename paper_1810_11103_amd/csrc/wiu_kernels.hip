@@ -326,11 +326,13 @@ hipError_t launch_sweep(int scheme, int dir, int variant, const SweepArgs& a, hi
 }
 
 hipError_t launch_wave_max(const Dims& d, const double* U, const double* M, double gam, unsigned long long* lx,
-                           unsigned long long* le, unsigned long long* cfl, int* status, hipStream_t st) {
+                           unsigned long long* le, unsigned long long* cfl, int* status, hipStream_t st,
+                           bool cleared) {
   // clear the maxima (a fill kernel, not a memset, so the sequence can be captured)
   const long long n = (long long)d.nx + d.ny + 1;
   // lx, le and cfl are contiguous in the workspace: lx[ny], le[nx], cfl[1]
-  hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, lx, n, 0ull);
+  if (!cleared)
+    hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, lx, n, 0ull);
   dim3 grid((d.nx + 63) / 64, (d.ny + 15) / 16);
   hipLaunchKernelGGL(wave_max_kernel, grid, dim3(64, 4), 0, st, d, U, M, gam, lx, le, cfl, status);
   return hipGetLastError();

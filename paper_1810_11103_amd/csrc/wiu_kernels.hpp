@@ -53,6 +53,31 @@ struct SweepArgs {
   unsigned long long* ncfl;
 };
 
+// Beyond the sweep's arguments: what a launch of stage tiles (wiu_stage.hpp)
+// does around its stage.
+struct StageArgs {
+  SweepArgs s;                       // mode 1 (dU/dt) or 2 (RK stage); Rxi is not used
+  // when set, the step size is cfl / max of these ncflw words, which the first
+  // workgroup also writes to dt_out; otherwise s.dt[0] is read
+  const unsigned long long* cflw;
+  int ncflw;
+  double cfl;
+  double* dt_out;
+  unsigned long long* clear;         // when set, `nclear` words to zero (the maxima of the stage after next)
+  long long nclear;
+  double* copy;                      // when set, receives the stage's source state
+};
+
+// Grids of at most this many nodes step with the stage tiles, larger ones with
+// the sweeps.  RK3 steps with stage tiles / sweeps, microseconds: 5-2MP 27.5 /
+// 53.1 on 67 x 59 nodes, 39.1 / 60.4 on 195 x 187, 60.9 / 65.4 on 259 x 251,
+// 105 / 88 on 387 x 379; 7-4MP 83 / 85 and 3-1MP 50 / 59 on 259 x 251.  Below
+// the line the sweeps' time is the latency of their launches, above it the
+// tiles pay for their halos.
+constexpr long long STAGE_NODES = 1 << 16;
+bool use_stage_tiles(long long nodes);
+hipError_t launch_stage(int scheme, const StageArgs& a, hipStream_t st);
+
 // One block of a batched multi-block problem (device table entry).  The
 // table holds element offsets; kernels add them to the base pointers they
 // receive as arguments (pointers stored in memory would be generic and cost
@@ -130,8 +155,11 @@ hipError_t launch_fill_u64(unsigned long long* p, long long n, hipStream_t st);
 void sweep_tile_shape(int dir, int variant, int& na, int& nb);
 int scheme_extra(int scheme);
 int sweep_variants(int dir);
+// Line maxima lx[ny], le[nx] and the CFL maximum cfl[1] (contiguous) of U,
+// cleared first by a launch of its own unless `cleared`.
 hipError_t launch_wave_max(const Dims& d, const double* U, const double* M, double gam, unsigned long long* lx,
-                           unsigned long long* le, unsigned long long* cfl, int* status, hipStream_t st);
+                           unsigned long long* le, unsigned long long* cfl, int* status, hipStream_t st,
+                           bool cleared = false);
 hipError_t launch_metrics(const Dims& d, int scheme, double ah, const double* x, const double* y, double* M,
                           double* T, int* status, hipStream_t st);
 // Central metric operator of a scheme as an antisymmetric node stencil

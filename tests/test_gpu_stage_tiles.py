@@ -1,0 +1,99 @@
+"""Small grids step with 8 x 8 stage tiles (both directions in one launch),
+larger ones with the direction sweeps.  Tile edges, one-node directions,
+ragged tiles, every scheme, option and side rule on the small side; the sweeps
+just above the line.  Bars as elsewhere: rhs 1e-12 of each component's maximum
+against the oracle, one RK3 step 1e-11 of each component's increment."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1810_11103_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+SCHEMES = ["3-1MP", "3-2MP", "5-1MP", "5-2MP", "7-1MP", "7-2MP", "7-4MP", "7-6MP"]
+
+
+@pytest.fixture(scope="module")
+def wiu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no ROCm device")
+    from paper_1810_11103_amd import wenoiu
+    return wenoiu
+
+
+def dev(a):
+    import torch
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64).cuda()
+
+
+def check(orc, wiu, s, g, U, sides=None, fixed=None, **kw):
+    print("stage tiles", s, g.x.shape, g.bc, sides, kw, file=sys.stderr, flush=True)
+    M = orc.metrics(s, g.x, g.y, g.bc, g.period, alpha_h=kw.get("alpha_h", 1.0))
+    kw2 = dict(kw)
+    if sides:
+        kw2.update(sides=sides, fixed=fixed)
+    sol = wiu.Solver(g.x, g.y, s, g.bc, g.period, params=wiu.make_params(**kw), sides=sides, fixed=fixed)
+    ref = orc.rhs(s, U, M, g.bc, **kw2)
+    out = sol.rhs(dev(U)).cpu().numpy()
+    for c in range(4):
+        if np.abs(ref[c]).max() > 1e-12 * np.abs(ref).max():  # a component that vanishes identically has no scale
+            assert np.abs(out[c] - ref[c]).max() <= 1e-12 * np.abs(ref[c]).max(), c
+    dt = orc.cfl_dt(U, M, 0.5)
+    ref1 = orc.rk3_step(s, U, M, dt, g.bc, **kw2)
+    Ud = dev(U)
+    sol.rk3_step_cfl(Ud, 0.5)
+    assert abs(float(sol.dt[0]) / dt - 1.0) <= 1e-13
+    d = Ud.cpu().numpy()
+    for c in range(4):
+        if np.abs((ref1 - U)[c]).max() > 1e-12 * np.abs(ref1 - U).max():
+            assert np.abs(d[c] - ref1[c]).max() <= 1e-11 * np.abs((ref1 - U)[c]).max(), c
+    # several steps in a call equal one call per step, bit for bit
+    Us, Um = dev(U), dev(U)
+    dts = sol.rk3_steps_cfl(Um, 0.5, 4)
+    for q in range(4):
+        sol.rk3_step_cfl(Us, 0.5)
+        assert float(sol.dt[0]) == float(dts[q]), q
+    assert bool((Us == Um).all())
+    assert sol.status() == 0
+
+
+@pytest.mark.parametrize("s", SCHEMES)
+@pytest.mark.parametrize("shape", [(7, 9), (8, 8), (17, 15), (64, 1), (1, 33), (131, 126), (300, 218)])
+def test_periodic_tiles(orc, wiu, s, shape):
+    g = W.periodic_grid(*shape, (0, 10, 0, 10), A=0.2, seed=3)
+    check(orc, wiu, s, g, W.random_smooth_state(g, seed=5))
+
+
+@pytest.mark.parametrize("s", ["3-2MP", "5-1MP", "5-2MP", "7-4MP", "7-6MP"])
+@pytest.mark.parametrize("shape", [(9, 8), (23, 17), (285, 240)])
+def test_sides_tiles(orc, wiu, s, shape):
+    g = W.bounded_grid(*shape, A=0.2, seed=4, layers=2)
+    U = W.random_smooth_state(g, seed=6)
+    fixed = np.zeros((4, 4))
+    fixed[0] = [1.0, 0.4, 0.0, 2.6]
+    fixed[3] = [1.1, 0.3, -0.2, 2.7]
+    check(orc, wiu, s, g, U)
+    check(orc, wiu, s, g, U, sides=("fixed", "wall", "wall", "fixed"), fixed=fixed)
+
+
+@pytest.mark.parametrize("s", ["3-1MP", "5-1MP", "5-2MP", "7-1MP"])
+@pytest.mark.parametrize("kw", [dict(vars="conservative"), dict(vars="primitive", weights="z"), dict(split="sw"),
+                                dict(split="vl", vars="primitive"), dict(weights="z")])
+@pytest.mark.parametrize("shape", [(21, 13), (270, 250)])
+def test_options_tiles(orc, wiu, s, kw, shape):
+    g = W.periodic_grid(*shape, (0, 10, 0, 10), A=0.2, seed=7)
+    check(orc, wiu, s, g, W.random_smooth_state(g, seed=8), **kw)
+
+
+def test_other_metrics_flagged(wiu):
+    """Metrics of another scheme latch the status bit and leave the state alone."""
+    g = W.periodic_grid(20, 12, (0, 10, 0, 10), A=0.2, seed=9)
+    U = W.random_smooth_state(g, seed=1)
+    sol = wiu.Solver(g.x, g.y, "5-1MP", g.bc, g.period)
+    sol.scheme = "5-2MP"
+    Ud = dev(U)
+    sol.rk3_steps_cfl(Ud, 0.5, 3)
+    assert sol.status() == wiu.ST_SCHEME
+    assert np.array_equal(Ud.cpu().numpy(), U)
