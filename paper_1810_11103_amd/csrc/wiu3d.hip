@@ -14,7 +14,6 @@
 // dU/dt or the RK stage (and, in stages 1 and 2, the next stage's maxima).
 #include "wenoiu.h"
 
-#include <utility>
 #include "wiu_kernels.hpp"
 
 namespace wiu {
@@ -1159,12 +1158,12 @@ __global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
 }
 
 // Line maxima of the wave speeds in all three directions and the CFL
-// maximum.  One thread per (i, j) column walks a chunk of KC3 nodes along k
+// maximum.  One thread per (i, j) column walks a chunk of kc <= KC3 nodes along k
 // (the third grid dimension covers the chunks): zeta lines reduce in
 // registers over the chunk, xi lines across the wave (threads along i), eta
 // lines by atomics.
 constexpr int KC3 = 16;
-__global__ void __launch_bounds__(256) w3_max_kernel(Dims3 d, const double* __restrict__ U,
+__global__ void __launch_bounds__(256) w3_max_kernel(Dims3 d, int kc, const double* __restrict__ U,
                                                      const double* __restrict__ M, double gam,
                                                      unsigned long long* __restrict__ lam, int* __restrict__ status) {
   const int i = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -1176,7 +1175,7 @@ __global__ void __launch_bounds__(256) w3_max_kernel(Dims3 d, const double* __re
   unsigned long long* cflm = lz + (long long)d.n[0] * d.n[1];
   double smz = 0.0, cm = 0.0;
   bool bad = false;
-  const int k0 = blockIdx.z * KC3, k1 = min(k0 + KC3, d.n[2]);  // uniform over the block
+  const int k0 = blockIdx.z * kc, k1 = min(k0 + kc, d.n[2]);  // uniform over the block
   for (int k = k0; k < k1; ++k) {
     double sx = 0.0;
     if (act) {
@@ -1248,12 +1247,11 @@ Dims3 dims3(const wiu_grid3* g) {
   return d;
 }
 
-// Workspace: [status | line maxima, two buffers (this and the next RK
-// stage) | dt | big area], the big area holding either the metric scratch
+// Workspace: [status | line maxima, a ring of four sets (one per state) | dt | big area], the big area holding either the metric scratch
 // (inner derivatives, nodal band) or the stepping buffers (Racc, U1, U2).
 struct Ws3 {
-  size_t lam, lam2, dt, big, metric_dx, metric_t, metric_x, racc, u1, u2, total;
-  long long nlam;
+  size_t lam, dt, big, metric_dx, metric_t, metric_x, racc, u1, u2, total;
+  long long nlam, set;  // words of a maxima set in use, and from one set to the next
 };
 
 // A metric box: `band` beyond the grid along bounded directions, plus
@@ -1283,8 +1281,8 @@ Ws3 ws3(const wiu_grid3* g) {
   // a maxima set: the line maxima and the CFL maximum (nlam entries), then
   // the partial CFL maxima per j [ny] that several steps per call carry
   const size_t set = al3((w.nlam + g->ny) * 8);
-  w.lam2 = w.lam + set;  // the next RK stage's maxima
-  w.dt = w.lam2 + set;
+  w.set = (long long)(set / 8);
+  w.dt = w.lam + 4 * set;
   w.big = w.dt + A3;
   const int B = GHOST + METRIC_REACH;  // the widest band (Eq. 2.6) and operator
   const Box3 bx = box3(d, B, 2 * METRIC_REACH);
@@ -1371,11 +1369,16 @@ hipError_t pass3(int scheme, const S3Args& a, int D, int mode, hipStream_t st) {
   }
 }
 
-hipError_t maxima3(const Dims3& d, const double* U, const double* M, double gam, unsigned long long* lam,
-                   long long nlam, int* status, hipStream_t st) {
-  if (launch_fill_u64(lam, nlam, st) != hipSuccess) return hipErrorUnknown;
-  hipLaunchKernelGGL(w3_max_kernel, dim3((d.n[0] + 63) / 64, (d.n[1] + 3) / 4, (d.n[2] + KC3 - 1) / KC3), dim3(256),
-                     0, st, d, U, M, gam, lam, status);
+// Line maxima and the CFL maximum of U into a cleared set.  Each thread walks
+// KC3 nodes along k, fewer while that leaves the chip without blocks: on
+// 40 x 36 x 33 nodes 16 in a row left 27 blocks and took 34 us.
+hipError_t maxima3(const Dims3& d, const double* U, const double* M, double gam, unsigned long long* lam, int* status,
+                   hipStream_t st) {
+  const long long cols = (long long)((d.n[0] + 63) / 64) * ((d.n[1] + 3) / 4);
+  int kc = KC3;
+  while (kc > 1 && cols * ((d.n[2] + kc - 1) / kc) < 1024) kc >>= 1;
+  hipLaunchKernelGGL(w3_max_kernel, dim3((d.n[0] + 63) / 64, (d.n[1] + 3) / 4, (d.n[2] + kc - 1) / kc), dim3(256), 0,
+                     st, d, kc, U, M, gam, lam, status);
   return hipGetLastError();
 }
 
@@ -1411,33 +1414,33 @@ static int rk3_3d(const wiu_grid3* g, int scheme, const wiu_params* p, double* U
   const double* src[3] = {U, U1, U2};
   double* dst[3] = {U1, U2, U};
   const double ca[3] = {0.0, 0.75, 1.0 / 3.0}, cb[3] = {1.0, 0.25, 2.0 / 3.0};
-  // two maxima sets: sa holds the current state's, sb receives the next
-  // stage's; the first step's come from a separate pass
-  unsigned long long* sa = (unsigned long long*)(base + w.lam);
-  unsigned long long* sb = (unsigned long long*)(base + w.lam2);
-  if (maxima3(d, U, M, p->gamma, sa, w.nlam, a.status, st) != hipSuccess) return WIU_EHIP;
+  // maxima sets in a ring of four, one per state: all cleared at first, the
+  // three that a later step accumulates by the launch that forms its step
+  // size; the first step's maxima come from a separate pass
+  unsigned long long* sets = (unsigned long long*)(base + w.lam);
+  int c = 0;
+  auto set = [&](int k) { return sets + ((c + k) & 3) * w.set; };
+  if (launch_fill_u64(sets, 4 * w.set, st) != hipSuccess) return WIU_EHIP;
+  if (maxima3(d, U, M, p->gamma, sets, a.status, st) != hipSuccess) return WIU_EHIP;
   for (int step = 0; step < nsteps; ++step) {
     double* dts = cfl > 0.0 ? dt + step : dt;
     if (cfl > 0.0) {
-      const hipError_t e = step == 0 ? launch_cfl_dt(sa + w.nlam - 1, cfl, dts, st)
-                                     : launch_cfl_dt_lines(sa + w.nlam, d.n[1], cfl, dts, st);
+      const hipError_t e = step == 0 ? launch_step_begin(set(0) + w.nlam - 1, 1, cfl, dts, nullptr, 0, 0, 0, st)
+                                     : launch_step_begin(set(0) + w.nlam, d.n[1], cfl, dts, sets, w.set, 4, c, st);
       if (e != hipSuccess) return WIU_EHIP;
     }
     a.dt = dts;
-    for (int s = 0; s < 3; ++s) {
+    for (int s = 0; s < 3; ++s, c = (c + 1) & 3) {
       a.U = src[s]; a.out = dst[s]; a.ca = ca[s]; a.cb = cb[s];
-      a.lam = s == 1 ? sb : sa;  // the maxima of U, U1, U2
-      unsigned long long* next = s == 0 ? sb : (s == 1 ? sa : (step + 1 < nsteps ? sb : nullptr));
-      const bool with_cfl = s == 2 && next;
-      if (next && launch_fill_u64(next, w.nlam + (with_cfl ? d.n[1] : 0), st) != hipSuccess) return WIU_EHIP;
+      a.lam = set(0);  // the maxima of U, U1, U2
+      unsigned long long* next = s < 2 || step + 1 < nsteps ? set(1) : nullptr;
       for (int q = 0; q < 3; ++q) {  // zeta, eta, then xi, which writes the stage state
         const int D = 2 - q;
         a.nlam = D == 0 ? next : nullptr;
-        a.ncfl = D == 0 && with_cfl ? next + w.nlam : nullptr;
+        a.ncfl = D == 0 && s == 2 && next ? next + w.nlam : nullptr;
         if (pass3(scheme, a, D, q == 0 ? 0 : (q == 1 ? 1 : 3), st) != hipSuccess) return WIU_EHIP;
       }
     }
-    std::swap(sa, sb);
   }
   return WIU_OK;
 }
@@ -1504,7 +1507,8 @@ int wiu3_rhs(const wiu_grid3* g, int scheme, const wiu_params* p, const double* 
   sides3(g, a);
   options3(p, a);
   a.U0 = nullptr; a.dt = nullptr; a.ca = 0.0; a.cb = 1.0; a.status = (int*)base;
-  if (maxima3(d, U, M, p->gamma, (unsigned long long*)a.lam, w.nlam, a.status, st) != hipSuccess) return WIU_EHIP;
+  if (launch_fill_u64((unsigned long long*)a.lam, w.nlam, st) != hipSuccess) return WIU_EHIP;
+  if (maxima3(d, U, M, p->gamma, (unsigned long long*)a.lam, a.status, st) != hipSuccess) return WIU_EHIP;
   for (int q = 0; q < 3; ++q)  // zeta, eta, then xi, which writes dU/dt
     if (pass3(scheme, a, 2 - q, q == 0 ? 0 : (q == 1 ? 1 : 2), st) != hipSuccess) return WIU_EHIP;
   return WIU_OK;
@@ -1518,7 +1522,8 @@ int wiu3_cfl_dt(const wiu_grid3* g, const wiu_params* p, const double* U, const 
   const Ws3 w = ws3(g);
   char* base = (char*)ws;
   unsigned long long* lam = (unsigned long long*)(base + w.lam);
-  if (maxima3(d, U, M, p->gamma, lam, w.nlam, (int*)base, st) != hipSuccess) return WIU_EHIP;
+  if (launch_fill_u64(lam, w.nlam, st) != hipSuccess) return WIU_EHIP;
+  if (maxima3(d, U, M, p->gamma, lam, (int*)base, st) != hipSuccess) return WIU_EHIP;
   return rc3(launch_cfl_dt(lam + w.nlam - 1, cfl, dt, st));
 }
 

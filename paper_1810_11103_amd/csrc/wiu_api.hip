@@ -7,7 +7,6 @@
 #include <string.h>
 
 #include <mutex>
-#include <utility>
 #include <vector>
 
 using namespace wiu;
@@ -67,14 +66,13 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 //   0            header: int status, padding
 //   HDR          lam_xi[ny], lam_eta[nx], cfl_max[1], cfl per eta line[nx]
 //                (uint64 bit patterns)
-//   lam2, lam3   two more such sets (maxima of RK stage states; the sets are
-//                contiguous, lam3 is used by the stage tiles only)
+//   lam2 .. lam4 three more such sets, contiguous (maxima of RK stage states)
 //   off_scratch  R^xi[4 np], U1[4 np], U2[4 np]  -- or the metric band temp
 //   then the adjoint region: Ubar2, Ubar1 (4 planes each), eigenvalue
 //   partials [max lines x segments] (double) and first maximal nodes (int),
 //   off-line contributions [max lines][2][6][4]
 struct WsLayout {
-  size_t lam, lam2, lam3, scratch, rxi, u1, u2, ub2, ub1, lpx, lpe, apx, ape, ghx, ghe, total;
+  size_t lam, lam2, set, scratch, rxi, u1, u2, ub2, ub1, lpx, lpe, apx, ape, ghx, ghe, total;
 };
 
 WsLayout layout(const wiu_grid* g) {
@@ -88,8 +86,8 @@ WsLayout layout(const wiu_grid* g) {
   const size_t set = align_up(((size_t)2 * g->nx + g->ny + 1) * 8);
   L.lam = ALIGN;
   L.lam2 = L.lam + set;
-  L.lam3 = L.lam2 + set;
-  L.scratch = L.lam3 + set;
+  L.set = set;
+  L.scratch = L.lam + 4 * set;
   L.rxi = L.scratch;
   L.u1 = L.rxi + plane4;
   L.u2 = L.u1 + plane4;
@@ -176,8 +174,11 @@ Dims dims(const wiu_grid* g) {
 struct Ws {
   int* status;
   unsigned long long *lx, *le, *cfl;
-  unsigned long long *lx2, *le2;  // maxima of an RK stage state, from the previous stage
-  unsigned long long* lx3;        // a third set (stage tiles), the same distance further
+  unsigned long long *lx2, *le2;  // a second set: maxima of an RK stage state, from the previous stage
+  // sets in all, contiguous from lx and `set` words apart: four, or in
+  // wiu_rk3_step_noalloc three with stage tiles and two with the sweeps
+  int nsets;
+  long long set;
   double *rxi, *u1, *u2, *band;
   double *ub2, *ub1, *lpx, *lpe, *ghx, *ghe;  // adjoint: per direction, eigenvalue partials and ghosts
   int *apx, *ape;                            //   and first maximal nodes
@@ -193,7 +194,8 @@ Ws carve(const wiu_grid* g, void* ws) {
   w.cfl = w.le + g->nx;
   w.lx2 = (unsigned long long*)(b + L.lam2);
   w.le2 = w.lx2 + g->ny;
-  w.lx3 = (unsigned long long*)(b + L.lam3);
+  w.nsets = 4;
+  w.set = (long long)(L.set / 8);
   w.rxi = (double*)(b + L.rxi);
   w.u1 = (double*)(b + L.u1);
   w.u2 = (double*)(b + L.u2);
@@ -260,13 +262,12 @@ struct Maxima {
   unsigned long long* wm = nullptr;  // target of the separate pass (lx[ny], le[nx], cfl[1]); default the workspace's
   bool cleared = false;              // nlx (and ncfl) are zero already
   // stage tiles only (StageArgs): the step size from CFL maxima, a set to
-  // clear for the stage after next, a copy of the source state
+  // clear for the stage after next
   const unsigned long long* cflw = nullptr;
   int ncflw = 0;
   double cfl = 0.0;
   double* dt_out = nullptr;
   unsigned long long* clear = nullptr;
-  double* copy = nullptr;
 };
 
 bool stage_tiles(const wiu_grid* g) { return use_stage_tiles((long long)g->nx * g->ny); }
@@ -307,7 +308,7 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
     t.s.status = w.status;
     t.s.nlam_xi = next ? mx.nlx : nullptr; t.s.nlam_eta = next ? mx.nle : nullptr; t.s.ncfl = next ? mx.ncfl : nullptr;
     t.cflw = mx.cflw; t.ncflw = mx.ncflw; t.cfl = mx.cfl; t.dt_out = mx.dt_out;
-    t.clear = mx.clear; t.nclear = set_words(g); t.copy = mx.copy;
+    t.clear = mx.clear; t.nclear = set_words(g);
     if (next && !mx.cleared && launch_fill_u64(mx.nlx, next_len, st) != hipSuccess) return WIU_EHIP;
     ProfScope ps(WIU_K_SWEEP_ETA, st);
     return hip_rc(launch_stage(scheme, t, st));
@@ -343,34 +344,35 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
 // the partial update P only at its own output node, so it may write the new
 // stage state over P: stage 1 puts P and then U1 in U1's buffer, stage 2 P
 // and U2 in U2's, and stage 3 its P in U1's buffer (U1 is no longer read).
-// Stage tiles use three maxima sets, all cleared by one launch: U's, U1's and
-// U2's own (or the record's).  With cfl > 0 the first stage forms the step size
-// from U's CFL maximum and writes it to dt.
+// The maxima of U, U1 and U2 go to sets of their own (or the record's), all
+// cleared by one launch; with two sets only, U2's go to U's once they are read,
+// and each is cleared by itself.  With cfl > 0 the first stage's step size is
+// formed from U's CFL maximum and written to dt.
 int rk3_stages(const wiu_grid* g, int scheme, const wiu_params* p, double* U, const double* M, double* dt, double* U1,
                double* U2, const Ws& w, hipStream_t st, double cfl = 0.0, unsigned long long* rec = nullptr,
                bool inplace = false) {
   const long long ns = (long long)g->nx + g->ny + 1;
-  const bool tiles = stage_tiles(g);
-  unsigned long long* m0 = rec ? rec : w.lx;                             // maxima of U
-  unsigned long long* mA = rec ? rec + ns : w.lx2;                       // of U1
-  unsigned long long* mB = rec ? rec + 2 * ns : (tiles ? w.lx3 : w.lx);  // of U2
-  if (tiles && launch_fill_u64(m0, mB + ns - m0, st) != hipSuccess) return WIU_EHIP;
+  const bool tiles = stage_tiles(g), three = rec || w.nsets > 2;
+  unsigned long long* m0 = rec ? rec : w.lx;                                      // maxima of U
+  unsigned long long* mA = rec ? rec + ns : w.lx2;                                // of U1
+  unsigned long long* mB = rec ? rec + 2 * ns : (three ? w.lx + 2 * w.set : w.lx);  // of U2
+  if (three && launch_fill_u64(m0, mB + ns - m0, st) != hipSuccess) return WIU_EHIP;
   {
     ProfScope ps(WIU_K_WAVE_MAX, st);
-    if (launch_wave_max(dims(g), U, M, p->gamma, m0, m0 + g->ny, m0 + ns - 1, w.status, st, tiles) != hipSuccess)
+    if (launch_wave_max(dims(g), U, M, p->gamma, m0, m0 + g->ny, m0 + ns - 1, w.status, st, three) != hipSuccess)
       return WIU_EHIP;
   }
   Ws w1 = w, w2 = w, w3 = w;
   if (inplace) { w1.rxi = U1; w2.rxi = U2; w3.rxi = U1; }
   Maxima m1;
   m1.lx_in = m0; m1.le_in = m0 + g->ny;
-  m1.nlx = mA; m1.nle = mA + g->ny; m1.cleared = tiles;
+  m1.nlx = mA; m1.nle = mA + g->ny; m1.cleared = three;
   if (cfl > 0.0 && tiles) { m1.cflw = m0 + ns - 1; m1.ncflw = 1; m1.cfl = cfl; m1.dt_out = dt; }
   if (cfl > 0.0 && !tiles && launch_cfl_dt(m0 + ns - 1, cfl, dt, st) != hipSuccess) return WIU_EHIP;
   int rc = residual(g, scheme, p, U, M, w1, 2, U1, U, dt, 0.0, 1.0, st, m1);
   if (rc) return rc;
   Maxima m2;
-  m2.lx_in = mA; m2.le_in = mA + g->ny; m2.nlx = mB; m2.nle = mB + g->ny; m2.cleared = tiles;
+  m2.lx_in = mA; m2.le_in = mA + g->ny; m2.nlx = mB; m2.nle = mB + g->ny; m2.cleared = three;
   rc = residual(g, scheme, p, U1, M, w2, 2, U2, U, dt, 0.75, 0.25, st, m2);
   if (rc) return rc;
   Maxima m3;
@@ -391,7 +393,7 @@ void* g_noalloc_ptr[NOALLOC_MAX_DEVICES] = {};
 // Layout in the scratch: two sets of line maxima (three with stage tiles),
 // then the two stage buffers (P / U1 and P / U2, see rk3_stages).
 struct NoallocLayout {
-  size_t lam, lam2, lam3, a, b, total;  // lam3: stage tiles only (small grids, far below the limit)
+  size_t lam, lam2, a, b, total;  // a third set follows lam2 with stage tiles (small grids, far below the limit)
 };
 NoallocLayout noalloc_layout(const wiu_grid* g) {
   NoallocLayout L;
@@ -399,7 +401,6 @@ NoallocLayout noalloc_layout(const wiu_grid* g) {
   const size_t lam = align_up(((size_t)g->nx + g->ny + 1) * 8);
   L.lam = 0;
   L.lam2 = lam;
-  L.lam3 = 2 * lam;
   L.a = (stage_tiles(g) ? 3 : 2) * lam;
   L.b = L.a + align_up(4 * np * 8);
   L.total = L.b + align_up(4 * np * 8);
@@ -511,20 +512,20 @@ int wiu_rk3_steps_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double
   Ws w = carve(g, ws);
   hipStream_t st = (hipStream_t)stream;
   const long long ny = g->ny, nxy = (long long)g->nx + g->ny;
-  // maxima sets (lam_xi[ny], lam_eta[nx], cfl[1], cfl per eta line[nx]): sa
-  // holds the current state's, sb receives the next stage's; they swap roles
-  // stage by stage.  The first step's come from the separate pass (one CFL
-  // maximum), later steps' from the step before (per-line CFL maxima).  Stage
-  // tiles rotate three sets: a stage clears the one its successor accumulates,
-  // whose last reader was its predecessor.
+  // Maxima sets (lam_xi[ny], lam_eta[nx], cfl[1], cfl per eta line[nx]) in a
+  // ring of four: each stage reads one and accumulates the next state's into
+  // the one after.  The first step's come from the separate pass (one CFL
+  // maximum), later steps' from the step before (per-line CFL maxima).  The
+  // sets are cleared together at first; later a step's three are cleared by the
+  // launch that forms its step size, or with stage tiles by the stage before
+  // the one that accumulates them (whose last reader was the stage before).
   const bool tiles = stage_tiles(g);
-  unsigned long long* sa = w.lx;
-  unsigned long long* sb = w.lx2;
-  unsigned long long* sc = tiles ? w.lx3 : w.lx;
-  if (tiles && launch_fill_u64(sa, sb + set_words(g) - sa, st) != hipSuccess) return WIU_EHIP;
+  int c = 0;
+  auto set = [&](int k) { return w.lx + ((c + k) & 3) * w.set; };
+  if (launch_fill_u64(w.lx, 4 * w.set, st) != hipSuccess) return WIU_EHIP;
   {
     ProfScope ps(WIU_K_WAVE_MAX, st);
-    if (launch_wave_max(dims(g), U, M, p->gamma, sa, sa + ny, sa + nxy, w.status, st, tiles) != hipSuccess)
+    if (launch_wave_max(dims(g), U, M, p->gamma, w.lx, w.lx + ny, w.lx + nxy, w.status, st, true) != hipSuccess)
       return WIU_EHIP;
   }
   const double ca[3] = {0.0, 0.75, 1.0 / 3.0}, cb[3] = {1.0, 0.25, 2.0 / 3.0};
@@ -532,24 +533,21 @@ int wiu_rk3_steps_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double
   double* dst[3] = {w.u1, w.u2, U};
   for (int s = 0; s < nsteps; ++s) {
     double* dt = dt_dev + s;
-    const unsigned long long* cflw = s == 0 ? sa + nxy : sa + nxy + 1;
-    if (!tiles && (s == 0 ? launch_cfl_dt(cflw, cfl, dt, st) : launch_cfl_dt_lines(cflw, g->nx, cfl, dt, st)) != hipSuccess)
+    const unsigned long long* cflw = s == 0 ? set(0) + nxy : set(0) + nxy + 1;
+    const int ncflw = s == 0 ? 1 : g->nx;
+    if (!tiles && launch_step_begin(cflw, ncflw, cfl, dt, s == 0 ? nullptr : w.lx, w.set, 4, c, st) != hipSuccess)
       return WIU_EHIP;
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < 3; ++q, c = (c + 1) & 3) {
       Maxima m;  // of the source state in, of the new one out (unless last)
-      m.lx_in = sa; m.le_in = sa + ny;
+      m.lx_in = set(0); m.le_in = m.lx_in + ny;
       if (q < 2 || s + 1 < nsteps) {
-        m.nlx = sb; m.nle = sb + ny;
-        if (q == 2) m.ncfl = sb + nxy + 1;
-        if (tiles) { m.cleared = true; m.clear = sc; }
+        m.nlx = set(1); m.nle = m.nlx + ny; m.cleared = true;
+        if (q == 2) m.ncfl = m.nlx + nxy + 1;
+        if (tiles) m.clear = set(2);
       }
-      if (tiles && q == 0) { m.cflw = cflw; m.ncflw = s == 0 ? 1 : g->nx; m.cfl = cfl; m.dt_out = dt; }
+      if (tiles && q == 0) { m.cflw = cflw; m.ncflw = ncflw; m.cfl = cfl; m.dt_out = dt; }
       const int rc = residual(g, scheme, p, src[q], M, w, 2, dst[q], U, dt, ca[q], cb[q], st, m);
       if (rc) return rc;
-      unsigned long long* last = sa;  // free now
-      sa = sb;
-      sb = tiles ? sc : last;
-      sc = last;
     }
   }
   return WIU_OK;
@@ -575,7 +573,8 @@ int wiu_rk3_step_noalloc(const wiu_grid* g, int scheme, const wiu_params* p, dou
   w.cfl = w.le + g->nx;
   w.lx2 = (unsigned long long*)(b + L.lam2);
   w.le2 = w.lx2 + g->ny;
-  w.lx3 = (unsigned long long*)(b + L.lam3);
+  w.nsets = stage_tiles(g) ? 3 : 2;
+  w.set = (long long)((L.lam2 - L.lam) / 8);
   double* A = (double*)(b + L.a);
   double* B = (double*)(b + L.b);
   // every maxima set is cleared before it is accumulated, and both stage
@@ -616,31 +615,29 @@ int wiu_rk3_steps_stages(const wiu_grid* g, int scheme, const wiu_params* p, dou
   const size_t plane4 = (size_t)4 * g->nx * g->ny;
   unsigned long long* r = (unsigned long long*)recs;
   // the first step's maxima of U from a separate pass, into its record;
-  // later steps' from the last stage of the step before.  Stage tiles have all
-  // records cleared by one launch and copy U_n as they stage it.
-  const bool tiles = stage_tiles(g);
-  if (tiles && launch_fill_u64(r, 3 * ns * nsteps, st) != hipSuccess) return WIU_EHIP;
+  // later steps' from the last stage of the step before.  All records are
+  // cleared by one launch.  U_n is stored by the step before writing it to its
+  // place among the stages; only the first is copied there.
+  if (launch_fill_u64(r, 3 * ns * nsteps, st) != hipSuccess) return WIU_EHIP;
   {
     ProfScope ps(WIU_K_WAVE_MAX, st);
-    if (launch_wave_max(dims(g), U, M, p->gamma, r, r + ny, r + ns - 1, w.status, st, tiles) != hipSuccess)
+    if (launch_wave_max(dims(g), U, M, p->gamma, r, r + ny, r + ns - 1, w.status, st, true) != hipSuccess)
       return WIU_EHIP;
   }
+  if (hipMemcpyAsync(stages, U, plane4 * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess) return WIU_EHIP;
   const double ca[3] = {0.0, 0.75, 1.0 / 3.0}, cb[3] = {1.0, 0.25, 2.0 / 3.0};
   for (int s = 0; s < nsteps; ++s) {
     double* S0 = stages + (size_t)s * 3 * plane4;
     double* S1 = S0 + plane4;
     double* S2 = S1 + plane4;
-    const double* src[3] = {U, S1, S2};
-    double* dst[3] = {S1, S2, U};
-    if (!tiles && hipMemcpyAsync(S0, U, plane4 * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
-      return WIU_EHIP;
+    const double* src[3] = {S0, S1, S2};
+    double* dst[3] = {S1, S2, s + 1 < nsteps ? S2 + plane4 : U};
     for (int q = 0; q < 3; ++q) {
       unsigned long long* rs = r + (3 * (long long)s + q) * ns;
       Maxima m;  // of the source state in, of the new one into the record after (unless last)
       m.lx_in = rs; m.le_in = rs + ny;
-      if (q < 2 || s + 1 < nsteps) { m.nlx = rs + ns; m.nle = rs + ns + ny; m.cleared = tiles; }
-      if (tiles && q == 0) m.copy = S0;
-      const int rc = residual(g, scheme, p, src[q], M, w, 2, dst[q], U, dt_dev, ca[q], cb[q], st, m);
+      if (q < 2 || s + 1 < nsteps) { m.nlx = rs + ns; m.nle = rs + ns + ny; m.cleared = true; }
+      const int rc = residual(g, scheme, p, src[q], M, w, 2, dst[q], S0, dt_dev, ca[q], cb[q], st, m);
       if (rc) return rc;
     }
   }

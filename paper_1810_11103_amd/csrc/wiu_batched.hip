@@ -20,9 +20,10 @@ struct wiu_plan {
   int4* d_tiles = nullptr;       // xi tiles, then eta tiles, then wave-max tiles
   int n_xi = 0, n_eta = 0, n_wm = 0;
   char* d_ws = nullptr;          // per-block lam, R^xi, U1, U2, dt; status
-  unsigned long long* d_lam = nullptr;   // line maxima of all blocks (stages 1 and 3)
-  unsigned long long* d_lam2 = nullptr;  // second set (stage 2), filled by stage 1's eta sweep
-  long long lam_len = 0;
+  // line maxima of all blocks, three sets `lam_set` words apart: of U, and of
+  // U1 and U2 as the eta sweeps of stages 1 and 2 write them
+  unsigned long long* d_lam = nullptr;
+  long long lam_len = 0, lam_set = 0;
   double* d_dt = nullptr;
   double* U_all = nullptr;        // caller's states and metrics (offsets in the block table)
   const double* M_all = nullptr;
@@ -151,6 +152,7 @@ BatchArgs base_args(const wiu_plan* p) {
   a.M_all = p->M_all;
   a.ws = (double*)p->d_ws;
   a.lam = p->d_lam;
+  a.lam_set = p->lam_set;
   a.xi_mode = 3;
   return a;
 }
@@ -159,23 +161,21 @@ int launch_step(wiu_plan* p, hipStream_t st) {
   BatchArgs a = base_args(p);
   // Line maxima: a separate pass for the step's state only; the eta sweeps
   // of stages 1 and 2 accumulate the maxima of the stage state they write
-  // (into lam2, then back into lam), which the next stage reads.
+  // into the next set, which the next stage reads.  One launch clears all.
   for (int stage = 0; stage < 3; ++stage) {
     a.stage = stage;
     if (stage == 0) {
-      if (launch_fill_u64(p->d_lam, p->lam_len, st) != hipSuccess) return WIU_EHIP;
+      if (launch_fill_u64(p->d_lam, 2 * p->lam_set + p->lam_len, st) != hipSuccess) return WIU_EHIP;
       a.tiles = p->d_tiles + p->n_xi + p->n_eta; a.ntiles = p->n_wm;
       if (launch_batched_wave_max(a, st) != hipSuccess) return WIU_EHIP;
       if (launch_group_max(p->d_lam, p->d_gstart, p->d_gmem, p->ngroups, st) != hipSuccess) return WIU_EHIP;
     }
     a.tiles = p->d_tiles; a.ntiles = p->n_xi;
     if (launch_batched_sweep(p->scheme, 0, p->variant[0], a, st) != hipSuccess) return WIU_EHIP;
-    if (stage < 2 && launch_fill_u64(stage == 0 ? p->d_lam2 : p->d_lam, p->lam_len, st) != hipSuccess)
-      return WIU_EHIP;
     a.tiles = p->d_tiles + p->n_xi; a.ntiles = p->n_eta;
     if (launch_batched_sweep(p->scheme, 1, p->variant[1], a, st) != hipSuccess) return WIU_EHIP;
     if (stage < 2 &&
-        launch_group_max(stage == 0 ? p->d_lam2 : p->d_lam, p->d_gstart, p->d_gmem, p->ngroups, st) != hipSuccess)
+        launch_group_max(p->d_lam + (stage + 1) * p->lam_set, p->d_gstart, p->d_gmem, p->ngroups, st) != hipSuccess)
       return WIU_EHIP;
   }
   return WIU_OK;
@@ -208,7 +208,7 @@ int wiu_batched_plan(const wiu_block* blocks, int nblocks, int scheme, const wiu
   p->variant[1] = eta_variant;
   p->params = *params;
 
-  // workspace: [status | lam, lam2 of all blocks | dt of all blocks | per block R^xi, U1, U2]
+  // workspace: [status | three maxima sets of all blocks | dt of all blocks | per block R^xi, U1, U2]
   std::vector<size_t> off_lam(nblocks), off_st(nblocks);
   size_t lam_total = 0;
   for (int b = 0; b < nblocks; ++b) {
@@ -217,9 +217,7 @@ int wiu_batched_plan(const wiu_block* blocks, int nblocks, int scheme, const wiu
   }
   size_t pos = ALIGN;                                   // status
   const size_t lam_pos = pos;
-  pos += align_up(lam_total * 8);
-  const size_t lam2_pos = pos;
-  pos += align_up(lam_total * 8);
+  pos += 3 * align_up(lam_total * 8);
   const size_t dt_pos = pos;
   pos += align_up((size_t)nblocks * 8);
   for (int b = 0; b < nblocks; ++b) {
@@ -228,14 +226,14 @@ int wiu_batched_plan(const wiu_block* blocks, int nblocks, int scheme, const wiu
     p->cells += (long long)blocks[b].nx * blocks[b].ny;
   }
   if (hipMalloc(&p->d_ws, pos) != hipSuccess) { free_plan(p); return WIU_EHIP; }
-  if (hipMemset(p->d_ws, 0, ALIGN + 2 * align_up(lam_total * 8) + align_up((size_t)nblocks * 8)) != hipSuccess) {
+  if (hipMemset(p->d_ws, 0, ALIGN + 3 * align_up(lam_total * 8) + align_up((size_t)nblocks * 8)) != hipSuccess) {
     free_plan(p);
     return WIU_EHIP;
   }
   p->d_status = (int*)p->d_ws;
   p->d_lam = (unsigned long long*)(p->d_ws + lam_pos);
-  p->d_lam2 = (unsigned long long*)(p->d_ws + lam2_pos);
   p->lam_len = (long long)lam_total;
+  p->lam_set = (long long)(align_up(lam_total * 8) / 8);
   p->d_dt = (double*)(p->d_ws + dt_pos);
 
   p->U_all = U_all;
@@ -255,7 +253,6 @@ int wiu_batched_plan(const wiu_block* blocks, int nblocks, int scheme, const wiu
     B.oU2 = (long long)((off_st[b] + 2 * plane4) / 8);
     B.oDt = (long long)(dt_pos / 8) + b;
     B.oLam = (long long)off_lam[b];
-    B.oLam2 = (long long)((lam2_pos - lam_pos) / 8 + off_lam[b]);
     for (int s = 0; s < 4; ++s) {
       const bool per = (s < 2 ? blocks[b].bc_x : blocks[b].bc_y) == WIU_BC_PERIODIC;
       B.side[s] = per ? WIU_SIDE_TRANSMISSIVE : blocks[b].side[s];

@@ -39,12 +39,11 @@ __global__ void __launch_bounds__(NA * NB, (sweep_waves<SC, OPT>())) batched_swe
     SweepArgs s;
     s.d = ufirst(B.d);
     s.M = b.M_all + ufirst(B.oM);
-    // stage 1 reads the maxima of the separate pass (lam) and accumulates
-    // those of U1 into lam2; stage 2 reads lam2 and accumulates into lam;
-    // stage 3 reads lam
-    const unsigned long long* lam = b.lam + ufirst(st == 1 ? B.oLam2 : B.oLam);
+    // stage 1 reads the maxima of the separate pass; each stage but the last
+    // accumulates those of the state it writes into the next set
+    unsigned long long* lam = b.lam + (st * b.lam_set + ufirst(B.oLam));
     s.lam_xi = lam; s.lam_eta = lam + s.d.ny;
-    unsigned long long* nlam = (DIR == 1 && st < 2) ? b.lam + ufirst(st == 0 ? B.oLam2 : B.oLam) : nullptr;
+    unsigned long long* nlam = (DIR == 1 && st < 2) ? lam + b.lam_set : nullptr;
     s.nlam_xi = nlam; s.nlam_eta = nlam ? nlam + s.d.ny : nullptr;
     s.ncfl = nullptr;
     s.gamma = b.gamma; s.alpha = b.alpha; s.eps = b.eps; s.ppm = b.ppm; s.vars = b.vars; s.ah = b.ah;

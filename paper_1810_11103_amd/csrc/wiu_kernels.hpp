@@ -65,7 +65,6 @@ struct StageArgs {
   double* dt_out;
   unsigned long long* clear;         // when set, `nclear` words to zero (the maxima of the stage after next)
   long long nclear;
-  double* copy;                      // when set, receives the stage's source state
 };
 
 // Grids of at most this many nodes step with the stage tiles, larger ones with
@@ -86,7 +85,7 @@ struct BlockDev {
   Dims d;
   long long oU, oM;              // state in U_all, metrics in M_all
   long long oRxi, oU1, oU2, oDt; // R^xi / partial stage update, stage states, dt: in ws
-  long long oLam, oLam2;         // two sets of line maxima (lam_xi[ny], lam_eta[nx], cfl[1]) in lam
+  long long oLam;                // line maxima (lam_xi[ny], lam_eta[nx], cfl[1]) in a set of lam
   // sides of non-periodic directions: rule (WIU_SIDE_*), fixed states, and
   // for interfaces the neighbour block and the affine map of ghost layer m
   // on line l to the neighbour's node, g0 + m gm + l gl
@@ -109,7 +108,8 @@ struct BatchArgs {
   double* U_all;             // bases of the offsets in BlockDev
   const double* M_all;
   double* ws;
-  unsigned long long* lam;
+  unsigned long long* lam;   // maxima of U; those of U1, U2 one and two sets further
+  long long lam_set;
   int xi_mode;               // sweep mode of the xi launches (3); a kernel argument
                              // rather than a constant, which keeps the epilogue lean
 };
@@ -183,8 +183,11 @@ hipError_t launch_group_max(unsigned long long* lam, const int* start, const int
 void* prof_open(int id, hipStream_t st);
 void prof_close(void* h);
 hipError_t launch_cfl_dt(const unsigned long long* cfl_max, double cfl, double* dt, hipStream_t st);
-// dt = cfl / max of n per-line CFL maxima
-hipError_t launch_cfl_dt_lines(const unsigned long long* cfl_lines, int n, double cfl, double* dt, hipStream_t st);
+// Begins a step: dt = cfl / max of n CFL maxima and, when `sets` is given, of
+// `nsets` maxima sets of `set` words there all but number `keep` cleared (the
+// words read belong to that one).
+hipError_t launch_step_begin(const unsigned long long* cflw, int n, double cfl, double* dt, unsigned long long* sets,
+                             long long set, int nsets, int keep, hipStream_t st);
 hipError_t launch_lambda_out(const Dims& d, double alpha, const unsigned long long* lx, const unsigned long long* le,
                              double* ox, double* oe, hipStream_t st);
 hipError_t launch_set_tag(const Dims& d, int scheme, double ah, double* M, hipStream_t st);

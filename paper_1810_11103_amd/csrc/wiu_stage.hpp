@@ -341,7 +341,6 @@ WIU_DEV void stage_tile(const StageArgs& a, int bx, int by, int wg, int nwg, Sta
         const double us = L.sq[c][(tj + SLO) * BW + ti + SLO];
         const double un = s.cb * (us + dt * (Rx * rj));
         Qn[c] = (s.ca == 0.0 ? un : s.ca * L.op[1 + c][tid] + un) + s.cb * (dt * (Re * rj));
-        if (a.copy) a.copy[c * d.np + o] = us;
       }
       s.out[c * d.np + o] = Qn[c];
     }
