@@ -543,6 +543,18 @@ WIU_DEV void flux3(const double Q[5], const double k[3], double gam, double E[5]
   E[4] = (Q[4] + p) * U;
 }
 
+// Lax-Friedrichs half flux (E^ + sl Q)/2, as half_flux in two dimensions.
+WIU_DEV void half_flux3(const double Q[5], const double k[3], double sl, double gam, double F[5]) {
+  const double h[3] = {0.5 * k[0], 0.5 * k[1], 0.5 * k[2]}, hs = 0.5 * sl;
+  const double ri = rcp(Q[0]);
+  const double u = Q[1] * ri, v = Q[2] * ri, w = Q[3] * ri;
+  const double p = (gam - 1.0) * (Q[4] - 0.5 * (Q[1] * u + Q[2] * v + Q[3] * w));
+  const double U = h[0] * u + h[1] * v + h[2] * w;
+  F[0] = Q[0] * U + hs * Q[0];
+  for (int a = 0; a < 3; ++a) F[1 + a] = Q[1 + a] * U + h[a] * p + hs * Q[1 + a];
+  F[4] = (Q[4] + p) * U + hs * Q[4];
+}
+
 // |k . u| + c |k| without contraction (every kernel rounds it alike).
 WIU_DEV double speed3(const double Q[5], const double k[3], double gam, bool& bad) {
 #pragma clang fp contract(off)
@@ -639,8 +651,8 @@ WIU_DEV void side_flux3(QF q, int side, const double n[3], const double mk[3], d
   const double gm1 = gam - 1.0;
   const double rr = rcp(Qr[0]);
   const double V[3] = {Qr[1] * rr, Qr[2] * rr, Qr[3] * rr};
-  const double q2 = V[0] * V[0] + V[1] * V[1] + V[2] * V[2];
-  const double p = gm1 * (Qr[4] - 0.5 * Qr[0] * q2);
+  const double hq = 0.5 * (V[0] * V[0] + V[1] * V[1] + V[2] * V[2]);
+  const double p = gm1 * (Qr[4] - Qr[0] * hq);
   const double c2 = gam * p * rr;
   const double rc = rsqrt_(c2);
   const double c = c2 * rc;
@@ -648,8 +660,8 @@ WIU_DEV void side_flux3(QF q, int side, const double n[3], const double mk[3], d
   const double qn = V[0] * n[0] + V[1] * n[1] + V[2] * n[2];
   const double qa = V[0] * t2[0] + V[1] * t2[1] + V[2] * t2[2];
   const double qb = V[0] * t1[0] + V[1] * t1[1] + V[2] * t1[2];
-  const double b1 = gm1 * (rc * rc);
-  const double b2 = 0.5 * b1 * q2;
+  // halves, as in the 2-D side flux: A and B below are halved too
+  const double b1 = 0.5 * gm1 * (rc * rc), b2 = b1 * hq, hrc = 0.5 * rc;
   // window slots of the stencil in interpolation order (left-biased for side
   // 0, mirrored for side 1); the reference slot has zero deviation
   // r = 2: k-2 .. k+1, r = 3: k-2 .. k+2, r = 4: k-3 .. k+3 (for side 0)
@@ -667,12 +679,12 @@ WIU_DEV void side_flux3(QF q, int side, const double n[3], const double mk[3], d
     for (int cc = 0; cc < 5; ++cc) dq[cc] = q(slot, cc) - Qr[cc];
     const double dmV = V[0] * dq[1] + V[1] * dq[2] + V[2] * dq[3];
     const double A = b2 * dq[0] - b1 * (dmV - dq[4]);
-    const double Bn = rc * (qn * dq[0] - (n[0] * dq[1] + n[1] * dq[2] + n[2] * dq[3]));
-    w[0][s] = 0.5 * (A + Bn);
-    w[1][s] = dq[0] - A;
+    const double Bn = hrc * (qn * dq[0] - (n[0] * dq[1] + n[1] * dq[2] + n[2] * dq[3]));
+    w[0][s] = A + Bn;
+    w[1][s] = fma(-2.0, A, dq[0]);
     w[2][s] = t2[0] * dq[1] + t2[1] * dq[2] + t2[2] * dq[3] - qa * dq[0];
     w[3][s] = t1[0] * dq[1] + t1[1] * dq[2] + t1[2] * dq[3] - qb * dq[0];
-    w[4][s] = 0.5 * (A - Bn);
+    w[4][s] = A - Bn;
   }
   double Wf[5];
 #pragma unroll
@@ -681,17 +693,15 @@ WIU_DEV void side_flux3(QF q, int side, const double n[3], const double mk[3], d
     else if constexpr (R == 3) Wf[f] = weno5<ZOK>(w[f][0], w[f][1], w[f][3], w[f][4], eps, ppm);
     else Wf[f] = weno7<ZOK>(w[f][0], w[f][1], w[f][2], w[f][4], w[f][5], w[f][6], eps, ppm);
   }
-  // Q = Q_ref + R W
-  const double s04 = Wf[0] + Wf[4], d40 = Wf[4] - Wf[0];
+  // Q = Q_ref + R W (W undoing its scale)
+  constexpr double ws = 1.0 / WSCALE<R>;
+  const double s04 = Wf[0] + Wf[4], cd = c * (Wf[4] - Wf[0]);
   const double sum = s04 + Wf[1];
   double r[5];
-  r[0] = Qr[0] + sum;
-  for (int a = 0; a < 3; ++a) r[1 + a] = Qr[1 + a] + (V[a] * sum + c * n[a] * d40 + t2[a] * Wf[2] + t1[a] * Wf[3]);
-  r[4] = Qr[4] + (H * s04 + c * qn * d40 + 0.5 * q2 * Wf[1] + qa * Wf[2] + qb * Wf[3]);
-  double E[5];
-  flux3(r, mk, gam, E);
-  const double sl = side == 0 ? lam : -lam;
-  for (int a = 0; a < 5; ++a) F[a] = 0.5 * (E[a] + sl * r[a]);
+  r[0] = fma(ws, sum, Qr[0]);
+  for (int a = 0; a < 3; ++a) r[1 + a] = fma(ws, V[a] * sum + n[a] * cd + t2[a] * Wf[2] + t1[a] * Wf[3], Qr[1 + a]);
+  r[4] = fma(ws, H * s04 + qn * cd + hq * Wf[1] + qa * Wf[2] + qb * Wf[3], Qr[4]);
+  half_flux3(r, mk, side == 0 ? lam : -lam, gam, F);
   if (split != 0) {
     double G[5];
     mid_split_alt3(split, r, mk, side, gam, G);
@@ -737,7 +747,7 @@ WIU_DEV void side_flux3_comp(QF q, int side, int vars, const double mk[3], doubl
     if constexpr (R == 2) W = weno3<ZOK>(w[f][0], w[f][1], w[f][3], eps, ppm);
     else if constexpr (R == 3) W = weno5<ZOK>(w[f][0], w[f][1], w[f][3], w[f][4], eps, ppm);
     else W = weno7<ZOK>(w[f][0], w[f][1], w[f][2], w[f][4], w[f][5], w[f][6], eps, ppm);
-    Vm[f] = Vr[f] + W;
+    Vm[f] = fma(1.0 / WSCALE<R>, W, Vr[f]);
   }
   double r[5];
   if (vars == 2) {
@@ -747,10 +757,7 @@ WIU_DEV void side_flux3_comp(QF q, int side, int vars, const double mk[3], doubl
   } else {
     for (int a = 0; a < 5; ++a) r[a] = Vm[a];
   }
-  double E[5];
-  flux3(r, mk, gam, E);
-  const double sl = side == 0 ? lam : -lam;
-  for (int a = 0; a < 5; ++a) F[a] = 0.5 * (E[a] + sl * r[a]);
+  half_flux3(r, mk, side == 0 ? lam : -lam, gam, F);
   if (split != 0) {
     double G[5];
     mid_split_alt3(split, r, mk, side, gam, G);
@@ -829,8 +836,9 @@ template <int SC, int DIR, int NA, int NB, bool OPT = false> struct Sweep3Lds {
 // U_out = ca U0 + cb (U + dt dU/dt).  Four block-wide barriers on every path
 // (five in an xi pass that accumulates the next stage's maxima).
 // OPT: compiled with the scheme options (a.vars, a.ah, a.weights); without
-// it the sweep runs the paper's configuration and carries no code for them.
-template <int SC, int DIR, int NA, int NB, bool OPT>
+// it the sweep runs the paper's configuration and carries no code for them, and
+// PPM says whether the weights are mapped.
+template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
 __global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
   __shared__ Sweep3Lds<SC, DIR, NA, NB, OPT> L;
   using R_ = Range<SC>;
@@ -838,7 +846,7 @@ __global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
   constexpr int OUT = NA - R_::EXTRA, QL = R_::QL, NQ = LT::NQ, NT = NA * NB;
   const Dims3& d = a.d;
   const double ah = OPT ? a.ah : 1.0;
-  const int ppm = OPT && a.weights != 0 ? 2 : a.ppm;  // 2: WENO-Z weights
+  const int ppm = OPT ? (a.weights != 0 ? 2 : a.ppm) : PPM;  // 2: WENO-Z weights
   const int split = OPT ? a.split : 0;                 // another split of the leading midpoint flux
   if (!tag3_ok(d, a.M, SC, ah)) {  // block-uniform
     if (threadIdx.x == 0 && threadIdx.y == 0) atomicOr(a.status, ST_SCHEME);
@@ -1327,7 +1335,7 @@ dim3 box_grid(const Box3& b) { return dim3((unsigned)(((b.w[0] * b.w[1] + 255) /
 
 // Tile shapes: xi 64 items x 4 lines (lanes along the line, one line per
 // wave), eta and zeta 32 items x 8 lines (lanes across the lines, along i).
-template <int SC, int DIR, int NA, int NB, bool OPT>
+template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
 hipError_t launch_sweep3_t(const S3Args& a, int mode, hipStream_t st) {
   constexpr int OUT = NA - Range<SC>::EXTRA;
   const int n = a.d.n[DIR];
@@ -1336,23 +1344,23 @@ hipError_t launch_sweep3_t(const S3Args& a, int mode, hipStream_t st) {
   const long long tiles = (long long)((n + OUT - 1) / OUT) * ((nac + NB - 1) / NB) * nb;
   const dim3 block = DIR == 0 ? dim3(NA, NB) : dim3(NB, NA);
   void* h = prof_open(WIU_K_SWEEP3, st);
-  hipLaunchKernelGGL((s3_sweep_kernel<SC, DIR, NA, NB, OPT>), dim3((unsigned)tiles), block, 0, st, a, mode);
+  hipLaunchKernelGGL((s3_sweep_kernel<SC, DIR, NA, NB, OPT, PPM>), dim3((unsigned)tiles), block, 0, st, a, mode);
   prof_close(h);
   return hipGetLastError();
 }
 
-template <int SC, bool OPT>
+template <int SC, bool OPT, bool PPM>
 hipError_t launch_pass3_o(const S3Args& a, int D, int mode, hipStream_t st) {
-  if (D == 0) return launch_sweep3_t<SC, 0, 64, 4, OPT>(a, mode, st);
-  if (D == 1) return launch_sweep3_t<SC, 1, 32, 8, OPT>(a, mode, st);
-  return launch_sweep3_t<SC, 2, 32, 8, OPT>(a, mode, st);
+  if (D == 0) return launch_sweep3_t<SC, 0, 64, 4, OPT, PPM>(a, mode, st);
+  if (D == 1) return launch_sweep3_t<SC, 1, 32, 8, OPT, PPM>(a, mode, st);
+  return launch_sweep3_t<SC, 2, 32, 8, OPT, PPM>(a, mode, st);
 }
 
 // the options kernels only when an option is in use
 template <int SC>
 hipError_t launch_pass3(const S3Args& a, int D, int mode, hipStream_t st) {
-  if (a.vars != 0 || a.ah != 1.0 || a.weights != 0 || a.split != 0) return launch_pass3_o<SC, true>(a, D, mode, st);
-  return launch_pass3_o<SC, false>(a, D, mode, st);
+  if (a.vars != 0 || a.ah != 1.0 || a.weights != 0 || a.split != 0) return launch_pass3_o<SC, true, true>(a, D, mode, st);
+  return a.ppm ? launch_pass3_o<SC, false, true>(a, D, mode, st) : launch_pass3_o<SC, false, false>(a, D, mode, st);
 }
 
 hipError_t pass3(int scheme, const S3Args& a, int D, int mode, hipStream_t st) {

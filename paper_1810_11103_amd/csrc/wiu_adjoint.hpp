@@ -181,8 +181,8 @@ WIU_DEV void side_flux_vjp(QF q, int side, double nx_, double ny_, double mx, do
   double W[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    if constexpr (FIFTH) W[k] = weno5(wv(k, 0), wv(k, 1), wv(k, 3), wv(k, 4), eps, ppm);
-    else W[k] = weno3(wv(k, 0), wv(k, 1), wv(k, 3), eps, ppm);
+    if constexpr (FIFTH) W[k] = weno5(wv(k, 0), wv(k, 1), wv(k, 3), wv(k, 4), eps, ppm) * (1.0 / WSCALE<3>);
+    else W[k] = weno3(wv(k, 0), wv(k, 1), wv(k, 3), eps, ppm) * (1.0 / WSCALE<2>);
   }
   const double s03 = W[0] + W[3], d30 = W[3] - W[0];
   const double sum = s03 + W[1];

@@ -250,19 +250,19 @@ __global__ void lambda_out_kernel(Dims d, double alpha, const unsigned long long
 // U_out = P - b dt R^eta/J^{-1}, so U0 is read by the lighter xi epilogue.
 // Launched for 4 waves per SIMD (at most 128 VGPRs).
 // ===========================================================================
-template <int SC, int DIR, int NA, int NB, bool OPT>
+template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
 __global__ void __launch_bounds__(NA * NB, (sweep_waves<SC, OPT>())) sweep_kernel(SweepArgs s) {
   __shared__ SweepLds<SC, DIR, NA, NB, OPT> lds;
   // logical tile in XCD-aware order
   const int total = gridDim.x * gridDim.y;
   const int lid = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, total);
-  sweep_tile<SC, DIR, NA, NB, OPT>(s, lid % gridDim.x, lid / gridDim.x, lds);
+  sweep_tile<SC, DIR, NA, NB, OPT, PPM>(s, lid % gridDim.x, lid / gridDim.x, lds);
 }
 
 // ---------------------------------------------------------------------------
 // Launch helpers
 // ---------------------------------------------------------------------------
-template <int SC, int DIR, int NA, int NB, bool OPT>
+template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
 hipError_t launch_sweep_t(const SweepArgs& a, hipStream_t st) {
   constexpr int OUT = NA - Range<SC>::EXTRA;
   const int n_al = DIR == 0 ? a.d.nx : a.d.ny;
@@ -271,15 +271,15 @@ hipError_t launch_sweep_t(const SweepArgs& a, hipStream_t st) {
   const int nlin = (n_ac + NB - 1) / NB;
   dim3 grid = DIR == 0 ? dim3(nseg, nlin) : dim3(nlin, nseg);
   dim3 block = DIR == 0 ? dim3(NA, NB) : dim3(NB, NA);
-  hipLaunchKernelGGL((sweep_kernel<SC, DIR, NA, NB, OPT>), grid, block, 0, st, a);
+  hipLaunchKernelGGL((sweep_kernel<SC, DIR, NA, NB, OPT, PPM>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
 // Tile shape `variant` of each direction (WIU_XI_TILES / WIU_ETA_TILES).
-template <int SC, int DIR, bool OPT>
+template <int SC, int DIR, bool OPT, bool PPM>
 hipError_t launch_sweep_vo(int variant, const SweepArgs& a, hipStream_t st) {
 #define WIU_CASE(v, na, nb) \
-  case v: return launch_sweep_t<SC, DIR, na, nb, OPT>(a, st);
+  case v: return launch_sweep_t<SC, DIR, na, nb, OPT, PPM>(a, st);
   if constexpr (DIR == 0) {
     switch (variant) {
       WIU_XI_TILES(WIU_CASE)
@@ -297,8 +297,8 @@ hipError_t launch_sweep_vo(int variant, const SweepArgs& a, hipStream_t st) {
 // the options kernels only when an option is in use
 template <int SC, int DIR>
 hipError_t launch_sweep_v(int variant, const SweepArgs& a, hipStream_t st) {
-  if (a.vars != 0 || a.ah != 1.0 || a.weights != 0 || a.split != 0) return launch_sweep_vo<SC, DIR, true>(variant, a, st);
-  return launch_sweep_vo<SC, DIR, false>(variant, a, st);
+  if (a.vars != 0 || a.ah != 1.0 || a.weights != 0 || a.split != 0) return launch_sweep_vo<SC, DIR, true, true>(variant, a, st);
+  return a.ppm ? launch_sweep_vo<SC, DIR, false, true>(variant, a, st) : launch_sweep_vo<SC, DIR, false, false>(variant, a, st);
 }
 
 int sweep_variants(int dir) { return dir == 0 ? WIU_N_XI_TILES : WIU_N_ETA_TILES; }

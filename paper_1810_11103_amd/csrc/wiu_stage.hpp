@@ -85,7 +85,7 @@ WIU_DEV void stage_state(const SweepArgs& s, int i, int j, double Q[4]) {
 
 // Tile (bx, by); a block of NT threads, all of which call it.  `first`: this
 // workgroup writes the step size; clearing is shared by workgroup `wg` of `nwg`.
-template <int SC, int TX, int TY, int NT, bool OPT>
+template <int SC, int TX, int TY, int NT, bool OPT, bool PPM>
 WIU_DEV void stage_tile(const StageArgs& a, int bx, int by, int wg, int nwg, StageLds<SC, TX, TY, OPT>& L) {
   using T = Traits<SC>;
   using LT = StageLds<SC, TX, TY, OPT>;
@@ -98,7 +98,7 @@ WIU_DEV void stage_tile(const StageArgs& a, int bx, int by, int wg, int nwg, Sta
   const int ow = min(TX, d.nx - i0), oh = min(TY, d.ny - j0);
   const double ah = OPT ? s.ah : 1.0;
   const bool alt = OPT && s.split != 0;
-  const int ppm = OPT && s.weights != 0 ? 2 : s.ppm;
+  const int ppm = OPT ? (s.weights != 0 ? 2 : s.ppm) : PPM;
   const double gam = s.gamma;
 
   // Task t < 2 MD is a side flux (midpoint t % MD, side t / MD), then come the

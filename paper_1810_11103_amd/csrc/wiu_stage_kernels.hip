@@ -12,28 +12,30 @@ namespace wiu {
 // by 512 lanes: 31.8, 32.8, 52.7.
 constexpr int ST_X = 8, ST_Y = 8, ST_UNITS = 256;
 
-template <int SC, int NT, bool OPT>
+template <int SC, int NT, bool OPT, bool PPM>
 __global__ void __launch_bounds__(NT) stage_kernel(StageArgs a) {
   __shared__ StageLds<SC, ST_X, ST_Y, OPT> lds;
   const int ntx = (a.s.d.nx + ST_X - 1) / ST_X;
   const int lid = xcd_remap(blockIdx.x, gridDim.x);
-  stage_tile<SC, ST_X, ST_Y, NT, OPT>(a, lid % ntx, lid / ntx, lid, gridDim.x, lds);
+  stage_tile<SC, ST_X, ST_Y, NT, OPT, PPM>(a, lid % ntx, lid / ntx, lid, gridDim.x, lds);
 }
 
-template <int SC, bool OPT> void launch_stage_o(const StageArgs& a, hipStream_t st) {
+template <int SC, bool OPT, bool PPM> void launch_stage_o(const StageArgs& a, hipStream_t st) {
   const Dims& d = a.s.d;
   const int tiles = ((d.nx + ST_X - 1) / ST_X) * ((d.ny + ST_Y - 1) / ST_Y);
   if (tiles <= ST_UNITS)
-    hipLaunchKernelGGL((stage_kernel<SC, 384, OPT>), dim3(tiles), dim3(384), 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<SC, 384, OPT, PPM>), dim3(tiles), dim3(384), 0, st, a);
   else
-    hipLaunchKernelGGL((stage_kernel<SC, 256, OPT>), dim3(tiles), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<SC, 256, OPT, PPM>), dim3(tiles), dim3(256), 0, st, a);
 }
 
 template <int SC> hipError_t launch_stage_s(const StageArgs& a, hipStream_t st) {
   if (a.s.vars != 0 || a.s.ah != 1.0 || a.s.weights != 0 || a.s.split != 0)
-    launch_stage_o<SC, true>(a, st);
+    launch_stage_o<SC, true, true>(a, st);
+  else if (a.s.ppm)
+    launch_stage_o<SC, false, true>(a, st);
   else
-    launch_stage_o<SC, false>(a, st);
+    launch_stage_o<SC, false, false>(a, st);
   return hipGetLastError();
 }
 

@@ -198,12 +198,17 @@ WIU_DEV void fused_stage_out(const SweepArgs& s, SweepLds<SC, 1, NA, NB, OPT>& L
 // OPT: compiled with the scheme options (interpolation variables s.vars and
 // the free parameter s.ah); without it the tile runs the paper's
 // configuration (characteristic variables, alpha = 1) and carries no code
-// for the options, which keeps its register count down.
-template <int SC, int DIR, int NA, int NB, bool OPT>
+// for the options, which keeps its register count down.  PPM: without OPT,
+// the mapping is compiled in (or out) too: asked in every interpolation it cut
+// the fluxes into blocks that the compiler could not schedule across and held
+// 20 registers more.  With the shorter interpolation (weno5): 2048^2 WENOIU5-2MP,
+// two steps 2741 -> 2650 us and 1235 -> 1040 VALU instructions an item of the xi
+// sweep; 1000 x 760 WENOIU7-4MP, one step 414 -> 385 us.
+template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
 WIU_DEV void sweep_tile(const SweepArgs& s, int bxl, int byl, SweepLds<SC, DIR, NA, NB, OPT>& L) {
   const double ah = OPT ? s.ah : 1.0;
   const bool alt = OPT && s.split != 0;                 // another midpoint split
-  const int ppm = OPT && s.weights != 0 ? 2 : s.ppm;    // 2: WENO-Z weights
+  const int ppm = OPT ? (s.weights != 0 ? 2 : s.ppm) : PPM;  // 2: WENO-Z weights
   using R_ = Range<SC>;
   constexpr int OUT = NA - R_::EXTRA;
   constexpr int NT = NA * NB;
