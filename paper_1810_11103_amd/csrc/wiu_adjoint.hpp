@@ -10,142 +10,142 @@
 namespace wiu {
 
 // ---------------------------------------------------------------------------
-// WENO r = 3 (inputs a, b, d, e around the zero centre) -- see weno5.
-// Accumulates the adjoints of the inputs.
+// WENO r = 3 (inputs a, b, d, e around the zero centre) -- see weno5, whose
+// scaled quantities are used throughout: with p_k the candidates times 8 c_k, E_k
+// = 4 (eps + IS_k) and D_k = E_k^2, P_k the products of the other two D, S_P =
+// sum c_k P_k, r = 1/S_P, x_k = 16 P_k r - 1, g_k = 1 + K_k x_k^3 (in units of
+// C_k), S = sum c_k g_k, N = sum g_k p_k, the value is out = N / (8 S).  Returns
+// out; v[] enters as the inputs and leaves as out's derivatives by them.
 // ---------------------------------------------------------------------------
-WIU_DEV void weno5_vjp(double a, double b, double d, double e, double eps, int ppm, double ob, double& ab,
-                       double& bb, double& db, double& eb) {
-  const double C[3] = {0.0625, 0.625, 0.3125};
-  const double KL[3] = {WIU_M3L0, WIU_M3L1, WIU_M3L2};
-  const double KH[3] = {WIU_M3H0, WIU_M3H1, WIU_M3H2};
-  const double p[3] = {0.375 * a - 1.25 * b, 0.375 * d - 0.125 * b, 0.75 * d - 0.125 * e};
-  const double d1 = b - a, d2 = -b, d3 = d, d4 = e - d;
-  const double t[3] = {d2 - d1, d3 - d2, d4 - d3};
-  const double s[3] = {fma(3.0, d2, -d1), -(d2 + d3), fma(-3.0, d3, d4)};
-  // IS_k = 13/12 t^2 + 1/4 s^2 (Eq. 3.22), E = eps + IS, D = E^2
+template <bool PPM> WIU_DEV double weno5_grad(double v[4], double eps) {
+  const double a = v[0], b = v[1], d = v[2], e = v[3];
+  const double c[3] = {1.0, 10.0, 5.0};
+  const double KL[3] = {WIU_M3L0 / 256.0, WIU_M3L1 * (0.625 * 0.625), WIU_M3L2 * (0.3125 * 0.3125)};
+  const double KH[3] = {WIU_M3H0 / 256.0, WIU_M3H1 * (0.625 * 0.625), WIU_M3H2 * (0.3125 * 0.3125)};
+  const double b10 = 10.0 * b, d30 = 30.0 * d;
+  const double p[3] = {fma(3.0, a, -b10), d30 - b10, fma(-5.0, e, d30)};
+  const double t[3] = {fma(-2.0, b, a), b + d, fma(-2.0, d, e)};
+  const double s[3] = {fma(-4.0, b, a), b - d, fma(-4.0, d, e)};
+  const double eps4 = 4.0 * eps;
   double E[3], D[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const double u = 0.5 * s[k];
-    E[k] = fma(13.0 / 12.0, t[k] * t[k], fma(u, u, eps));
+    E[k] = fma(13.0 / 3.0, t[k] * t[k], fma(s[k], s[k], eps4));
     D[k] = E[k] * E[k];
   }
-  // alpha_k = C_k prod_{l != k} D_l (the common factor of the products cancels)
   const double P[3] = {D[1] * D[2], D[0] * D[2], D[0] * D[1]};
-  const double al[3] = {C[0] * P[0], C[1] * P[1], C[2] * P[2]};
-  const double r = rcp_w(al[0] + al[1] + al[2]);
-  double w[3], g[3], h[3], dw[3];
+  const double r = rcp_w(fma(10.0, P[1], fma(5.0, P[2], P[0])));
+  const double r16 = 16.0 * r;
+  double x[3], g[3], gx[3];  // gx = dg/dx / 3
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    w[k] = al[k] * r;
-    dw[k] = w[k] - C[k];
-    h[k] = kd(dw[k], KL[k], KH[k]);  // K d, as the forward sweep forms it
-    g[k] = ppm ? fma(dw[k], fma(dw[k], h[k], -1.0), w[k]) : w[k];  // C + K d^3
+    x[k] = fma(P[k], r16, -1.0);
+    if (PPM) {
+      gx[k] = x[k] * kd(x[k], KL[k], KH[k]);
+      g[k] = fma(x[k], gx[k], 1.0);
+    } else {
+      gx[k] = 1.0 / 3.0;
+      g[k] = x[k] + 1.0;
+    }
   }
-  const double rs = rcp_w(g[0] + g[1] + g[2]);
+  const double rs = rcp_w(fma(10.0, g[1], fma(5.0, g[2], g[0])));
   const double N = g[0] * p[0] + g[1] * p[1] + g[2] * p[2];
-  // out = N / sum g
-  const double Nb = ob * rs;
-  const double sgb = -(Nb * N) * rs;
-  double pb[3], cb[3];
-  double rb = 0.0;
+  const double Nb = 0.125 * rs;
+  const double out = Nb * N;
+  const double Sb = -(out * rs);
+  double pb[3], z[3], T = 0.0;  // z = adjoint of x / 3
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     pb[k] = Nb * g[k];
-    const double gb = fma(Nb, p[k], sgb);
-    const double wb = ppm ? gb * (3.0 * (dw[k] * h[k])) : gb;  // dg/dw = 3 K d^2
-    cb[k] = wb * r;
-    rb = fma(wb, al[k], rb);
+    z[k] = fma(c[k], Sb, Nb * p[k]) * gx[k];
+    T = fma(x[k] + 1.0, z[k], T);
   }
-  const double Sb = -(rb * r) * r;
-  // adjoints of alpha_k times C_k, then of D_l
+  // x_k = 16 P_k / S_P - 1, then P_k of the D and D_k = E_k^2
+  const double q = 3.0 * r, q16 = 16.0 * q, SPb = -(q * T);
+  double Pb[3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) cb[k] = (cb[k] + Sb) * C[k];
-  const double Db[3] = {fma(cb[1], D[2], cb[2] * D[1]), fma(cb[0], D[2], cb[2] * D[0]),
-                        fma(cb[0], D[1], cb[1] * D[0])};
+  for (int k = 0; k < 3; ++k) Pb[k] = fma(q16, z[k], c[k] * SPb);
+  const double Db[3] = {fma(Pb[1], D[2], Pb[2] * D[1]), fma(Pb[0], D[2], Pb[2] * D[0]),
+                        fma(Pb[0], D[1], Pb[1] * D[0])};
   double tb[3], sb[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const double q = E[k] * Db[k];  // dIS = 2 E dD
-    tb[k] = (13.0 / 3.0) * q * t[k];
-    sb[k] = q * s[k];
+    const double f = 4.0 * (E[k] * Db[k]);
+    tb[k] = (13.0 / 3.0 * f) * t[k];
+    sb[k] = f * s[k];
   }
-  const double d1b = -tb[0] - sb[0];
-  const double d2b = tb[0] - tb[1] + 3.0 * sb[0] - sb[1];
-  const double d3b = tb[1] - tb[2] - sb[1] - 3.0 * sb[2];
-  const double d4b = tb[2] + sb[2];
-  ab += -d1b + 0.375 * pb[0];
-  bb += d1b - d2b - 1.25 * pb[0] - 0.125 * pb[1];
-  db += d3b - d4b + 0.375 * pb[1] + 0.75 * pb[2];
-  eb += d4b - 0.125 * pb[2];
+  const double p01 = pb[0] + pb[1], p12 = pb[1] + pb[2];
+  v[0] = fma(3.0, pb[0], tb[0] + sb[0]);
+  v[1] = fma(-10.0, p01, fma(-2.0, tb[0], fma(-4.0, sb[0], tb[1] + sb[1])));
+  v[2] = fma(30.0, p12, fma(-2.0, tb[2], fma(-4.0, sb[2], tb[1] - sb[1])));
+  v[3] = fma(-5.0, pb[2], tb[2] + sb[2]);
+  return out;
 }
 
-// WENO r = 2 (inputs a, b, d around the zero centre) -- see weno3.
-WIU_DEV void weno3_vjp(double a, double b, double d, double eps, int ppm, double ob, double& ab, double& bb,
-                       double& db) {
-  const double C[2] = {0.25, 0.75};
-  const double KL[2] = {WIU_M2L0, WIU_M2L1};
-  const double KH[2] = {WIU_M2H0, WIU_M2H1};
-  const double p[2] = {-0.5 * b, 0.5 * d};
-  const double d1 = b - a, d2 = -b, d3 = d;
-  const double t[2] = {d2 - d1, d3 - d2};
-  const double s[2] = {fma(3.0, d2, -d1), -(d2 + d3)};
+// WENO r = 2 (inputs a, b, d around the zero centre) -- see weno3: p = (-b, d),
+// P = (D_1, D_0), x_k = 4 P_k r - 1, g_k = 1 + K_k x_k^2 (in units of C_k), S =
+// g_0 + 3 g_1, out = (3 g_1 d - g_0 b) / (2 S).
+template <bool PPM> WIU_DEV double weno3_grad(double v[3], double eps) {
+  const double a = v[0], b = v[1], d = v[2];
+  const double KL[2] = {WIU_M2L0 * 0.25, WIU_M2L1 * 0.75};
+  const double KH[2] = {WIU_M2H0 * 0.25, WIU_M2H1 * 0.75};
+  const double t[2] = {fma(-2.0, b, a), b + d}, s[2] = {fma(-4.0, b, a), b - d};
+  const double eps4 = 4.0 * eps;
   double E[2], D[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    const double u = 0.5 * s[k];
-    E[k] = fma(13.0 / 12.0, t[k] * t[k], fma(u, u, eps));
+    E[k] = fma(13.0 / 3.0, t[k] * t[k], fma(s[k], s[k], eps4));
     D[k] = E[k] * E[k];
   }
-  const double al[2] = {C[0] * D[1], C[1] * D[0]};
-  const double r = rcp_w(al[0] + al[1]);
-  double w[2], g[2], h[2], dw[2];
+  const double r = rcp_w(fma(3.0, D[0], D[1])), r4 = 4.0 * r;
+  double x[2], g[2], gx[2];  // gx = dg/dx / 2
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    w[k] = al[k] * r;
-    dw[k] = w[k] - C[k];
-    h[k] = kd(dw[k], KL[k], KH[k]);  // K d, as the forward sweep forms it
-    g[k] = ppm ? fma(dw[k], h[k] - 1.0, w[k]) : w[k];  // C + K d^2
+    x[k] = fma(D[1 - k], r4, -1.0);
+    if (PPM) {
+      gx[k] = kd(x[k], KL[k], KH[k]);
+      g[k] = fma(x[k], gx[k], 1.0);
+    } else {
+      gx[k] = 0.5;
+      g[k] = x[k] + 1.0;
+    }
   }
-  const double rs = rcp_w(g[0] + g[1]);
-  const double N = g[0] * p[0] + g[1] * p[1];
-  // out = N / sum g
-  const double Nb = ob * rs;
-  const double sgb = -(Nb * N) * rs;
-  double pb[2], cb[2], rb = 0.0;
+  const double g1 = 3.0 * g[1];
+  const double rs = rcp_w(g[0] + g1);
+  const double Nb = 0.5 * rs;
+  const double out = Nb * (g1 * d - g[0] * b);
+  const double Sb = -(out * rs);
+  const double z0 = (Sb - Nb * b) * gx[0], z1 = 3.0 * ((Nb * d + Sb) * gx[1]);
+  const double T = fma(x[0], z0, z0) + fma(x[1], z1, z1);
+  const double q = 2.0 * r, q4 = 4.0 * q, SPb = -(q * T);
+  // P_0 = D_1, P_1 = D_0 with weights 1 and 3 in S_P; dD = 2 E dE
+  const double f1 = 4.0 * (E[1] * fma(q4, z0, SPb)), f0 = 4.0 * (E[0] * fma(q4, z1, 3.0 * SPb));
+  const double tb0 = (13.0 / 3.0 * f0) * t[0], sb0 = f0 * s[0], tb1 = (13.0 / 3.0 * f1) * t[1], sb1 = f1 * s[1];
+  v[0] = tb0 + sb0;
+  v[1] = fma(-2.0, tb0, fma(-4.0, sb0, tb1 + sb1)) - Nb * g[0];
+  v[2] = (tb1 - sb1) + Nb * g1;
+  return out;
+}
+
+// Orders two independent computations: what follows from b starts when a is done,
+// so that the four fields' reverses are not interleaved (their temporaries at once
+// are more than the register file holds).
+template <int N> WIU_DEV void one_after(double* a, double* b) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    pb[k] = Nb * g[k];
-    const double gb = fma(Nb, p[k], sgb);
-    const double wb = ppm ? gb * (2.0 * h[k]) : gb;  // dg/dw = 2 K d
-    cb[k] = wb * r;
-    rb = fma(wb, al[k], rb);
-  }
-  const double Sb = -(rb * r) * r;
-  // alpha_0 = C_0 D_1, alpha_1 = C_1 D_0; dIS = 2 E dD
-  const double q0 = E[0] * ((cb[1] + Sb) * C[1]), q1 = E[1] * ((cb[0] + Sb) * C[0]);
-  double tb[2], sb[2];
-  tb[0] = (13.0 / 3.0) * q0 * t[0]; sb[0] = q0 * s[0];
-  tb[1] = (13.0 / 3.0) * q1 * t[1]; sb[1] = q1 * s[1];
-  const double d1b = -tb[0] - sb[0];
-  const double d2b = tb[0] - tb[1] + 3.0 * sb[0] - sb[1];
-  const double d3b = tb[1] - sb[1];
-  ab += -d1b;
-  bb += d1b - d2b - 0.5 * pb[0];
-  db += d3b + 0.5 * pb[1];
+  for (int j = 0; j < N; ++j) asm volatile("" : "+v"(a[j]), "+v"(b[j]));
 }
 
 // ---------------------------------------------------------------------------
 // Reverse of side_flux for one side: given Fb = adjoint of F^{+-}_{k+1/2},
 // accumulate the adjoints of the states k-2 .. k+3 and of the line
 // eigenvalue.  The states are read through q(m, c) and the adjoints added
-// through qb(m, c, value), so both can live in LDS.  Per stencil node only
-// the five forward values A, B, drho, dm, dn of the projection are kept; the
-// characteristic values are rebuilt from them where needed.
+// through qb(m, c, value), so both can live in LDS.  The sixteen characteristic
+// values are projected once; each field's interpolation replaces its own by the
+// derivatives that the reverse needs.
 // ---------------------------------------------------------------------------
-template <bool FIFTH, class QF, class QBF>
+template <bool FIFTH, bool PPM, class QF, class QBF>
 WIU_DEV void side_flux_vjp(QF q, int side, double nx_, double ny_, double mx, double my, double lam, double gam,
-                           double eps, int ppm, const double Fb[4], QBF qb, double& lamb) {
+                           double eps, const double Fb[4], QBF qb, double& lamb) {
   const int mr = 2 + side;
   const double Qr[4] = {q(mr, 0), q(mr, 1), q(mr, 2), q(mr, 3)};
   const double gm1 = gam - 1.0;
@@ -162,27 +162,32 @@ WIU_DEV void side_flux_vjp(QF q, int side, double nx_, double ny_, double mx, do
   const double qt = v * nx_ - u * ny_;
   const double b1 = gm1 * (rc * rc);
   const double b2 = 0.5 * b1 * q2;
-  constexpr int NS = FIFTH ? 5 : 4;
-  // stencil slot s <-> state m (left-biased order for side 0, mirrored for 1);
-  // slot 2 is the reference node, whose deviation is zero
-  auto mof = [&](int s_) { return side == 0 ? s_ : 5 - s_; };
-  // characteristic value k of slot s_, recomputed from the staged states
-  // wherever it is needed (keeps the register working set small)
-  auto wv = [&](int k, int s_) {
-    const int m = mof(s_);
-    const double dr = q(m, 0) - Qr[0], dm = q(m, 1) - Qr[1], dn = q(m, 2) - Qr[2];
-    if (k == 2) return nx_ * dn - ny_ * dm - qt * dr;
-    const double de = q(m, 3) - Qr[3];
-    const double A = b2 * dr - b1 * (u * dm + v * dn - de);
-    if (k == 1) return dr - A;
-    const double B = rc * (qn * dr - nx_ * dm - ny_ * dn);
-    return k == 0 ? 0.5 * (A + B) : 0.5 * (A - B);
-  };
+  const double b1h = 0.5 * b1, b2h = 0.5 * b2, rch = 0.5 * rc;
+  // stencil entry j = 0..NV-1 <-> state m (left-biased order for side 0,
+  // mirrored for 1); the reference node, between entries 1 and 2, has none
+  constexpr int NV = FIFTH ? 4 : 3;
+  auto mof = [&](int j) { const int s_ = j < 2 ? j : j + 1; return side == 0 ? s_ : 5 - s_; };
+  double w[4][NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int m = mof(j);
+    const double dr = q(m, 0) - Qr[0], dm = q(m, 1) - Qr[1], dn = q(m, 2) - Qr[2], de = q(m, 3) - Qr[3];
+    const double A = b2h * dr - b1h * (u * dm + v * dn - de);  // halves of A and B
+    const double B = rch * (qn * dr - nx_ * dm - ny_ * dn);
+    w[0][j] = A + B;
+    w[1][j] = fma(-2.0, A, dr);
+    w[2][j] = nx_ * dn - ny_ * dm - qt * dr;
+    w[3][j] = A - B;
+  }
+  // WENO per characteristic component, one after the other: its value, and in
+  // place of its inputs their derivatives (an adjoint is linear in Wb, so one
+  // evaluation serves both passes)
   double W[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    if constexpr (FIFTH) W[k] = weno5(wv(k, 0), wv(k, 1), wv(k, 3), wv(k, 4), eps, ppm) * (1.0 / WSCALE<3>);
-    else W[k] = weno3(wv(k, 0), wv(k, 1), wv(k, 3), eps, ppm) * (1.0 / WSCALE<2>);
+    if (k) one_after<NV>(w[k - 1], w[k]);
+    if constexpr (FIFTH) W[k] = weno5_grad<PPM>(w[k], eps);
+    else W[k] = weno3_grad<PPM>(w[k], eps);
   }
   const double s03 = W[0] + W[3], d30 = W[3] - W[0];
   const double sum = s03 + W[1];
@@ -227,51 +232,48 @@ WIU_DEV void side_flux_vjp(QF q, int side, double nx_, double ny_, double mx, do
   const double Wb1 = 0.5 * q2 * r3b + sumb;
   double qtb = W[2] * r3b;
   const double Wb[4] = {s03b - d30b, Wb1, Wb2, s03b + d30b};
-  // WENO per characteristic component: wb[k][s] = adjoint of value k at slot s.
-  // The compiler barrier makes the reverse re-read the staged states instead
-  // of keeping every forward intermediate of the four components live.
-  double wb[4][NS];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    asm volatile("" ::: "memory");
 #pragma unroll
-    for (int s_ = 0; s_ < NS; ++s_) wb[k][s_] = 0.0;
-    if constexpr (FIFTH)
-      weno5_vjp(wv(k, 0), wv(k, 1), wv(k, 3), wv(k, 4), eps, ppm, Wb[k], wb[k][0], wb[k][1], wb[k][3], wb[k][4]);
-    else
-      weno3_vjp(wv(k, 0), wv(k, 1), wv(k, 3), eps, ppm, Wb[k], wb[k][0], wb[k][1], wb[k][3]);
+    for (int j = 0; j < NV; ++j) w[k][j] *= Wb[k];
   }
   // projection of the deviations: per slot, adjoints of A, B and of the
   // deviation itself, then onto the slot's state and the reference state
-  double b1b = 0.0, b2b = 0.0, rcb = 0.0;
+  // (A = b2 dr - b1 (u dm + v dn - de), B = rc (qn dr - nx dm - ny dn)); the
+  // coefficients' adjoints need only the sums of Ab, Bb and Wb_2 over the
+  // deviations
+  double Ar = 0.0, Am = 0.0, An = 0.0, Ae = 0.0, Br = 0.0, Bm = 0.0, Bn = 0.0, Tr = 0.0;
+  const double rcq = rc * qn;
 #pragma unroll
-  for (int s_ = 0; s_ < NS; ++s_) {
-    if (s_ == 2) continue;
+  for (int s_ = 0; s_ < NV; ++s_) {
     const int m = mof(s_);
     const double dr = q(m, 0) - Qr[0], dm = q(m, 1) - Qr[1], dn = q(m, 2) - Qr[2], de = q(m, 3) - Qr[3];
-    const double Ab = 0.5 * (wb[0][s_] + wb[3][s_]) - wb[1][s_];
-    const double Bb = 0.5 * (wb[0][s_] - wb[3][s_]);
-    double drb = wb[1][s_] - qt * wb[2][s_], dmb = -ny_ * wb[2][s_], dnb = nx_ * wb[2][s_], deb = 0.0;
-    qtb -= dr * wb[2][s_];
-    // A = b2 dr - b1 (u dm + v dn - de)
-    b2b += Ab * dr;
-    drb += Ab * b2;
-    b1b -= Ab * (u * dm + v * dn - de);
-    ub -= Ab * b1 * dm;
-    vb -= Ab * b1 * dn;
-    dmb -= Ab * b1 * u;
-    dnb -= Ab * b1 * v;
-    deb += Ab * b1;
-    // B = rc (qn dr - nx dm - ny dn)
-    rcb += Bb * (qn * dr - nx_ * dm - ny_ * dn);
-    qnb += Bb * rc * dr;
-    drb += Bb * rc * qn;
-    dmb -= Bb * rc * nx_;
-    dnb -= Bb * rc * ny_;
+    const double Ab = fma(0.5, w[0][s_] + w[3][s_], -w[1][s_]);
+    const double Bb = 0.5 * (w[0][s_] - w[3][s_]);
+    const double Tb = w[2][s_];
+    Ar = fma(Ab, dr, Ar);
+    Am = fma(Ab, dm, Am);
+    An = fma(Ab, dn, An);
+    Ae = fma(Ab, de, Ae);
+    Br = fma(Bb, dr, Br);
+    Bm = fma(Bb, dm, Bm);
+    Bn = fma(Bb, dn, Bn);
+    Tr = fma(Tb, dr, Tr);
+    const double deb = b1 * Ab, Bc = rc * Bb;
+    const double drb = fma(rcq, Bb, fma(b2, Ab, fma(-qt, Tb, w[1][s_])));
+    const double dmb = -fma(nx_, Bc, fma(u, deb, ny_ * Tb));
+    const double dnb = fma(nx_, Tb, -fma(ny_, Bc, v * deb));
     // deviation = q[m] - Qr
     qb(m, 0, drb); qb(m, 1, dmb); qb(m, 2, dnb); qb(m, 3, deb);
     Qrb[0] -= drb; Qrb[1] -= dmb; Qrb[2] -= dnb; Qrb[3] -= deb;
   }
+  const double b2b = Ar;
+  double b1b = Ae - fma(u, Am, v * An);
+  double rcb = fma(qn, Br, -fma(nx_, Bm, ny_ * Bn));
+  ub = fma(-b1, Am, ub);
+  vb = fma(-b1, An, vb);
+  qnb = fma(rc, Br, qnb);
+  qtb -= Tr;
   // reference state
   b1b += 0.5 * q2 * b2b;
   q2b += 0.5 * b1 * b2b;

@@ -34,7 +34,13 @@ template <int DIR, int NA, int NB> struct AdjLds {
   static WIU_DEV int ri(int tb, int pos) { return DIR == 0 ? tb * NR + pos : pos * NB + tb; }
 };
 
-template <int SC, int DIR, int NA, int NB>
+// 35.8 KB of LDS per 128 items leave two waves on a SIMD, so a wave's own chain of
+// dependent operations is what it runs at.  The mapping switch is compiled in, and
+// a characteristic field is interpolated once for both its value and its
+// derivatives: one residual's adjoint of 5-2MP on 512 x 512 nodes took 51.6 (xi) and
+// 50.4 us (eta) with the switch tested per field and the interpolation done twice,
+// 46.4 and 43.1 with the switch compiled in, 42.8 and 41.6 so.
+template <int SC, int DIR, int NA, int NB, bool PPM>
 __global__ void __launch_bounds__(NA * NB, 2) adj_sweep_kernel(AdjArgs s) {
   constexpr int LO = -3;                 // first item relative to the output segment
   constexpr int OUT = NA - 6;
@@ -195,7 +201,7 @@ __global__ void __launch_bounds__(NA * NB, 2) adj_sweep_kernel(AdjArgs s) {
         double Fb[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) Fb[c] = side == 0 ? Fpb[c] : Fmb[c];
-        side_flux_vjp<Traits<SC>::fifth>(q, side, nx_, ny_, mx, my, lam, s.gamma, s.eps, s.ppm, Fb, qb, lamb);
+        side_flux_vjp<Traits<SC>::fifth, PPM>(q, side, nx_, ny_, mx, my, lam, s.gamma, s.eps, Fb, qb, lamb);
       }
     }
   }
@@ -436,7 +442,10 @@ hipError_t launch_adj_t(const AdjArgs& a, hipStream_t st) {
   const int nlin = (n_ac + NB - 1) / NB;
   dim3 grid = DIR == 0 ? dim3(nseg, nlin) : dim3(nlin, nseg);
   dim3 block = DIR == 0 ? dim3(NA, NB) : dim3(NB, NA);
-  hipLaunchKernelGGL((adj_sweep_kernel<SC, DIR, NA, NB>), grid, block, 0, st, a);
+  if (a.ppm)
+    hipLaunchKernelGGL((adj_sweep_kernel<SC, DIR, NA, NB, true>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((adj_sweep_kernel<SC, DIR, NA, NB, false>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 

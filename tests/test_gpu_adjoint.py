@@ -76,6 +76,22 @@ def test_rhs_vjp_matches_oracle(orc, wiu, s, kind):
     assert np.all(err <= 1e-10), err
 
 
+@pytest.mark.parametrize("s", ["3-2MP", "5-2MP"])
+@pytest.mark.parametrize("kind", ["vortex_ragged", "riemann"])
+def test_rhs_vjp_without_mapping_matches_oracle(orc, wiu, s, kind):
+    """The sweeps compiled without the weight mapping; the bar of the mapped ones."""
+    say("rhs vjp without mapping", s, kind)
+    g, U = _case(kind)
+    M = orc.metrics(s, g.x, g.y, g.bc, g.period)
+    Gb = np.random.default_rng(13).standard_normal(U.shape)
+    ref = orc.rhs_vjp(s, U, M, Gb, g.bc, ppm=0)
+    sol = wiu.Solver(g.x, g.y, s, g.bc, g.period, params=wiu.make_params(ppm=0))
+    out = sol.rhs_vjp(_dev(U), _dev(Gb)).cpu().numpy()
+    assert sol.status() == 0
+    err = normwise(out, ref)
+    assert np.all(err <= 1e-10), err
+
+
 @pytest.mark.parametrize("s", ["3-1MP", "5-2MP"])
 def test_rhs_vjp_dot_product_with_oracle_tangent(orc, wiu, s):
     g, U = _case("riemann")
