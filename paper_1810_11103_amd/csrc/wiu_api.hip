@@ -67,7 +67,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 //   HDR          lam_xi[ny], lam_eta[nx], cfl_max[1], cfl per eta line[nx]
 //                (uint64 bit patterns)
 //   lam2 .. lam4 three more such sets, contiguous (maxima of RK stage states)
-//   off_scratch  R^xi[4 np], U1[4 np], U2[4 np]  -- or the metric band temp
+//   off_scratch  R^xi[4 np], U1[4 np], U2[4 np]
 //   then the adjoint region: Ubar2, Ubar1 (4 planes each), eigenvalue
 //   partials [max lines x segments] (double) and first maximal nodes (int),
 //   off-line contributions [max lines][2][6][4]
@@ -78,8 +78,6 @@ struct WsLayout {
 WsLayout layout(const wiu_grid* g) {
   WsLayout L;
   const size_t np = (size_t)g->nx * g->ny;
-  const int B = GHOST + 4;  // widest nodal-metric band (eight-point interpolation)
-  const size_t band = 5 * (size_t)(g->nx + 2 * B) * (g->ny + 2 * B);
   const size_t plane4 = align_up(4 * np * 8);
   // a maxima set: lam_xi[ny], lam_eta[nx], cfl[1], then per eta line the
   // CFL maxima[nx] that wiu_rk3_steps_cfl accumulates in a step's last stage
@@ -91,9 +89,7 @@ WsLayout layout(const wiu_grid* g) {
   L.rxi = L.scratch;
   L.u1 = L.rxi + plane4;
   L.u2 = L.u1 + plane4;
-  const size_t end_rk = L.u2 + plane4;
-  const size_t end_met = L.scratch + align_up(band * 8);
-  L.ub2 = end_rk > end_met ? end_rk : end_met;
+  L.ub2 = L.u2 + plane4;
   L.ub1 = L.ub2 + plane4;
   const size_t lp_xi = (size_t)g->ny * adj_nseg(0, g->nx), lp_eta = (size_t)g->nx * adj_nseg(1, g->ny);
   L.lpx = L.ub1 + plane4;
@@ -179,7 +175,7 @@ struct Ws {
   // wiu_rk3_step_noalloc three with stage tiles and two with the sweeps
   int nsets;
   long long set;
-  double *rxi, *u1, *u2, *band;
+  double *rxi, *u1, *u2;
   double *ub2, *ub1, *lpx, *lpe, *ghx, *ghe;  // adjoint: per direction, eigenvalue partials and ghosts
   int *apx, *ape;                            //   and first maximal nodes
 };
@@ -199,7 +195,6 @@ Ws carve(const wiu_grid* g, void* ws) {
   w.rxi = (double*)(b + L.rxi);
   w.u1 = (double*)(b + L.u1);
   w.u2 = (double*)(b + L.u2);
-  w.band = (double*)(b + L.scratch);
   w.ub2 = (double*)(b + L.ub2);
   w.ub1 = (double*)(b + L.ub1);
   w.lpx = (double*)(b + L.lpx);
@@ -454,7 +449,7 @@ int wiu_metrics(const wiu_grid* g, int scheme, const wiu_params* p, const double
   if (!grid_ok(g) || !scheme_ok(scheme) || !alpha_h_ok(scheme, ah) || !x || !y || !M || !ws) return WIU_EINVAL;
   Ws w = carve(g, ws);
   ProfScope ps(WIU_K_METRICS, (hipStream_t)stream);
-  return hip_rc(launch_metrics(dims(g), scheme, ah, x, y, M, w.band, w.status, (hipStream_t)stream));
+  return hip_rc(launch_metrics(dims(g), scheme, ah, x, y, M, w.status, (hipStream_t)stream));
 }
 
 int wiu_set_metrics_tag(const wiu_grid* g, int scheme, const wiu_params* p, double* M, wiu_stream_t stream) {

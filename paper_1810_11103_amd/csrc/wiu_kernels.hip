@@ -1,7 +1,7 @@
 // HIP kernels of libwenoiu for gfx950 (fp64 throughout, no MFMA: nothing on
 // this path is a dense contraction).
 //
-//   metrics_nodal_kernel / metrics_band_kernel  grid metrics (Secs. 2.2-2.4)
+//   metrics_kernel / metrics_band_kernel        grid metrics (Secs. 2.2-2.4)
 //   wave_max_kernel                             line maxima of |U^| + c|k^| and
 //                                               the CFL maximum (Sec. 2.3)
 //   sweep_kernel<scheme, dir>                   residual of one direction (Sec. 3)
@@ -30,63 +30,41 @@ WIU_DEV double shifted_diff(double c1, double c0, int k, double L) {
   return (s + (double)k * L) + e;
 }
 
-// Along one real line of n values c[stride * t]: difference X(a1) - X(a0)
-// for arbitrary integer a1, a0 under the boundary rule.  `shift` says whether
-// this coordinate is the one the period shifts (x along i, y along j).
-struct LineDiff {
-  const double* c;
-  long long stride;
-  int n, bc;
-  double L;
-  bool shift;
-  WIU_DEV double at(int t) const { return c[stride * t]; }
-  WIU_DEV double operator()(int a1, int a0) const {
-    if (bc == 0) {
-      int w1 = a1, k1 = 0, w0 = a0, k0 = 0;
-      while (w1 < 0) { w1 += n; --k1; }
-      while (w1 >= n) { w1 -= n; ++k1; }
-      while (w0 < 0) { w0 += n; --k0; }
-      while (w0 >= n) { w0 -= n; ++k0; }
-      return shifted_diff(at(w1), at(w0), shift ? (k1 - k0) : 0, L);
+// Along one line, at(t) its coordinate: the difference X(a1) - X(a0) under the
+// boundary rule.  at takes positions outside a periodic line (it wraps them), and
+// [0, n) of a transmissive one.  `shift` says whether this coordinate is the one
+// the period shifts (x along i, y along j).
+template <class At>
+WIU_DEV double line_diff(const At& at, int n, int bc, double L, bool shift, int a1, int a0) {
+  if (bc == 0) {
+    int turns = 0;
+    if (shift) {
+      for (int w = a1; w < 0; w += n) --turns;
+      for (int w = a1; w >= n; w -= n) ++turns;
+      for (int w = a0; w < 0; w += n) ++turns;
+      for (int w = a0; w >= n; w -= n) --turns;
     }
-    // transmissive: X(a) = X(clamp(a)) + (a - clamp(a)) * step at that end
-    int c1 = a1 < 0 ? 0 : (a1 >= n ? n - 1 : a1);
-    int c0 = a0 < 0 ? 0 : (a0 >= n ? n - 1 : a0);
-    double d = at(c1) - at(c0);
-    if (a1 != c1) d += (double)(a1 - c1) * (a1 < 0 ? at(1) - at(0) : at(n - 1) - at(n - 2));
-    if (a0 != c0) d -= (double)(a0 - c0) * (a0 < 0 ? at(1) - at(0) : at(n - 1) - at(n - 2));
-    return d;
+    return shifted_diff(at(a1), at(a0), turns, L);
   }
-};
-
-// Difference along i of coordinate array c (x or y) on row b (any integer):
-// rows outside a transmissive range extend linearly from the last two rows.
-WIU_DEV double diff_i(const Dims& d, const double* c, bool is_x, int b, int a1, int a0) {
-  auto row = [&](int r) {
-    LineDiff ld{c + (long long)r * d.nx, 1, d.nx, d.bcx, d.Lx, is_x};
-    return ld(a1, a0);
-  };
-  if (d.bcy == 0) return row(bc_index(b, d.ny, 0));
-  if (b < 0) { double d0 = row(0), d1 = row(1); return d0 + (double)b * (d1 - d0); }
-  if (b >= d.ny) {
-    double dl = row(d.ny - 1), d2 = row(d.ny - 2);
-    return dl + (double)(b - d.ny + 1) * (dl - d2);
-  }
-  return row(b);
+  // transmissive: X(a) = X(clamp(a)) + (a - clamp(a)) * step at that end
+  int c1 = a1 < 0 ? 0 : (a1 >= n ? n - 1 : a1);
+  int c0 = a0 < 0 ? 0 : (a0 >= n ? n - 1 : a0);
+  double d = at(c1) - at(c0);
+  if (a1 != c1) d += (double)(a1 - c1) * (a1 < 0 ? at(1) - at(0) : at(n - 1) - at(n - 2));
+  if (a0 != c0) d -= (double)(a0 - c0) * (a0 < 0 ? at(1) - at(0) : at(n - 1) - at(n - 2));
+  return d;
 }
 
-WIU_DEV double diff_j(const Dims& d, const double* c, bool is_y, int a, int b1, int b0) {
-  auto col = [&](int cidx) {
-    LineDiff ld{c + cidx, d.nx, d.ny, d.bcy, d.Ly, is_y};
-    return ld(b1, b0);
-  };
-  if (d.bcx == 0) return col(bc_index(a, d.nx, 0));
-  if (a < 0) { double d0 = col(0), d1 = col(1); return d0 + (double)a * (d1 - d0); }
-  if (a >= d.nx) {
-    double dl = col(d.nx - 1), d2 = col(d.nx - 2);
-    return dl + (double)(a - d.nx + 1) * (dl - d2);
+// f(r), a difference along the other direction on line r, for any line r of n:
+// lines outside a transmissive range extend linearly from the last two.
+template <class F> WIU_DEV double across(const F& f, int n, int bc, int r) {
+  if (bc == 0) return f(r);
+  if (r < 0) { double d0 = f(0), d1 = f(1); return d0 + (double)r * (d1 - d0); }
+  if (r >= n) {
+    double dl = f(n - 1), d2 = f(n - 2);
+    return dl + (double)(r - n + 1) * (dl - d2);
   }
-  return col(a);
+  return f(r);
 }
 
 // Each scheme's central operator delta^{c,(1)} (Eqs. 3.7, 3.9, 3.19, 3.21 and
@@ -132,37 +110,153 @@ MetricStencil metric_stencil(int scheme, double a) {
 // interpolation (3 for six points, 4 for eight).
 int metric_band(int scheme) { return GHOST + (scheme >= 4 ? 4 : 3); }
 
-// Nodal metrics on the band of width B around the grid: T[5][(ny+2B)(nx+2B)].
-// Periodic directions evaluate at the wrapped node so that band copies are
-// bitwise equal to the interior values.
-__global__ void metrics_nodal_kernel(Dims d, MetricStencil ms, int B, const double* __restrict__ x,
-                                     const double* __restrict__ y, double* __restrict__ T) {
-  const int W = d.nx + 2 * B, Hh = d.ny + 2 * B;
-  const int ta = blockIdx.x * blockDim.x + threadIdx.x;
-  const int tb = blockIdx.y * blockDim.y + threadIdx.y;
-  if (ta >= W || tb >= Hh) return;
-  int a = ta - B, b = tb - B;
-  if (d.bcx == 0) a = bc_index(a, d.nx, 0);
-  if (d.bcy == 0) b = bc_index(b, d.ny, 0);
-  double x_xi = 0.0, y_xi = 0.0, x_eta = 0.0, y_eta = 0.0;
-#pragma unroll
-  for (int m = 1; m <= METRIC_REACH; ++m) {
-    const double cm = ms.d[m - 1];
-    if (cm == 0.0) continue;
-    x_xi += cm * diff_i(d, x, true, b, a + m, a - m);
-    y_xi += cm * diff_i(d, y, false, b, a + m, a - m);
-    x_eta += cm * diff_j(d, x, false, a, b + m, b - m);
-    y_eta += cm * diff_j(d, y, true, a, b + m, b - m);
-  }
-  const long long P = (long long)W * Hh, o = (long long)tb * W + ta;
-  // Sec. 2.2 in two dimensions
-  T[0 * P + o] = y_eta;                          // xi_x^
-  T[1 * P + o] = -x_eta;                         // xi_y^
-  T[2 * P + o] = -y_xi;                          // eta_x^
-  T[3 * P + o] = x_xi;                           // eta_y^
-  T[4 * P + o] = x_xi * y_eta - x_eta * y_xi;    // J^{-1}
+// Nodal and midpoint metrics of a single grid on the stored band, in one pass: a
+// workgroup stages the coordinates of MT_X x MT_Y nodes and K around them in LDS,
+// forms the derivatives there (by xi on the rows and by eta on the columns that
+// the midpoint interpolation reaches too), and writes the nine planes.  Bound by
+// writing them: 5-2MP on 1531 x 1187 nodes takes 39.6 us (4.0 TB/s), 7-6MP on 2000 x
+// 1500 66.6.  As two kernels through five scratch planes, each derivative taken from
+// global memory with the boundary rule applied at every tap, these took 113.9 and
+// 202.7.  One node a lane: 32 x 16 with 256 lanes took 47.5 and 79.5, 64 x 16 with
+// 512 50.9 and 76.8; 32 x 8 with 256 lanes 41.3 and 76.2, 16 x 16 40.4 and 73.9.
+constexpr int MT_X = 32, MT_Y = 16, MT_THREADS = 512;
+
+template <int K, bool EIGHT> struct MetricLds {
+  static constexpr int LO = EIGHT ? 3 : 2, HI = EIGHT ? 4 : 3;  // reach of the interpolation
+  static constexpr int S = MT_X + 2 * K, R = MT_Y + 2 * K;
+  static constexpr int EX = MT_X + LO + HI, XY = MT_Y + LO + HI;
+  static_assert(K >= HI, "the staged nodes hold the interpolated ones");
+  double c[2][R * S];      // x, y
+  double e[2][MT_Y * EX];  // x_eta, y_eta
+  double x[2][XY * MT_X];  // x_xi, y_xi
+};
+
+// First staged position along a direction of n nodes for a tile at a0: a periodic
+// line is staged as it repeats, of a transmissive one the nodes that exist, so many
+// that the last two are among them wherever the tile passes the end.
+WIU_DEV int metric_origin(int a0, int K, int S, int n, int bc) {
+  return bc == 0 ? a0 - K : max(0, min(a0 - K, n - S));
 }
 
+template <int K, bool EIGHT>
+__global__ void __launch_bounds__(MT_THREADS) metrics_kernel(Dims d, MetricStencil ms, int scheme, double ah,
+                                                             const double* __restrict__ x,
+                                                             const double* __restrict__ y, double* __restrict__ M,
+                                                             int* __restrict__ status) {
+  using LT = MetricLds<K, EIGHT>;
+  constexpr int S = LT::S, R = LT::R, EX = LT::EX, XY = LT::XY, LO = LT::LO;
+  __shared__ LT L;
+  const int lid = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+  const int a0 = (lid % gridDim.x) * MT_X - GHOST, b0 = (lid / gridDim.x) * MT_Y - GHOST;
+  const int tid = threadIdx.x;
+  if (lid == 0 && tid == 0) {
+    double* tag = M + 9 * d.mplane;
+    tag[0] = TAG_MAGIC; tag[1] = (double)scheme; tag[2] = (double)d.nx; tag[3] = (double)d.ny;
+    tag[4] = (double)d.bcx; tag[5] = (double)d.bcy; tag[6] = ah; tag[7] = 0.0;
+  }
+  const bool inside = a0 >= K && a0 + MT_X + K <= d.nx && b0 >= K && b0 + MT_Y + K <= d.ny;
+  const int ox = metric_origin(a0, K, S, d.nx, d.bcx), oy = metric_origin(b0, K, R, d.ny, d.bcy);
+  {
+    constexpr int N = (R * S + MT_THREADS - 1) / MT_THREADS;
+    double v[2][N];
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      const int e = min(tid + it * MT_THREADS, R * S - 1);
+      const long long o =
+          (long long)bc_index(oy + e / S, d.ny, d.bcy) * d.nx + bc_index(ox + e % S, d.nx, d.bcx);
+      v[0][it] = x[o];
+      v[1][it] = y[o];
+    }
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      const int e = tid + it * MT_THREADS;
+      if (e < R * S) {
+        L.c[0][e] = v[0][it];
+        L.c[1][e] = v[1][it];
+      }
+    }
+  }
+  __syncthreads();
+  // derivatives along a direction with stride st between staged neighbours
+  auto central = [&](const double* c, int st) {
+    double s = 0.0;
+#pragma unroll
+    for (int m = 1; m <= K; ++m) s += ms.d[m - 1] * (c[m * st] - c[-m * st]);
+    return s;
+  };
+  auto at = [&](int q, int a, int b) { return L.c[q][(b - oy) * S + (a - ox)]; };
+  for (int e = tid; e < MT_Y * EX; e += MT_THREADS) {  // by eta, at (a, b)
+    const int ey = e / EX, ex = e % EX;
+    if (inside) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) L.e[q][e] = central(&L.c[q][(ey + K) * S + ex + K - LO], S);
+      continue;
+    }
+    const int a = a0 - LO + ex, b = b0 + ey;
+    if (a >= d.nx + GHOST + LT::HI || b >= d.ny + GHOST) continue;
+    for (int q = 0; q < 2; ++q) {
+      double s = 0.0;
+      for (int m = 1; m <= K; ++m)
+        s += ms.d[m - 1] * across([&](int r) {
+               return line_diff([&](int t) { return at(q, r, t); }, d.ny, d.bcy, d.Ly, q == 1, b + m, b - m);
+             }, d.nx, d.bcx, a);
+      L.e[q][e] = s;
+    }
+  }
+  for (int e = tid; e < XY * MT_X; e += MT_THREADS) {  // by xi, at (a, b)
+    const int ey = e / MT_X, ex = e % MT_X;
+    if (inside) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) L.x[q][e] = central(&L.c[q][(ey + K - LO) * S + ex + K], 1);
+      continue;
+    }
+    const int a = a0 + ex, b = b0 - LO + ey;
+    if (a >= d.nx + GHOST || b >= d.ny + GHOST + LT::HI) continue;
+    for (int q = 0; q < 2; ++q) {
+      double s = 0.0;
+      for (int m = 1; m <= K; ++m)
+        s += ms.d[m - 1] * across([&](int r) {
+               return line_diff([&](int t) { return at(q, t, r); }, d.nx, d.bcx, d.Lx, q == 0, a + m, a - m);
+             }, d.ny, d.bcy, b);
+      L.x[q][e] = s;
+    }
+  }
+  __syncthreads();
+  // midpoint metrics: the interpolation in the metric's own direction
+  auto mid = [&](const double* c, int st) {
+    auto v = [&](int l) { return c[l * st]; };
+    if constexpr (EIGHT)
+      return (-5.0 * (v(-3) + v(4)) + 49.0 * (v(-2) + v(3)) - 245.0 * (v(-1) + v(2)) + 1225.0 * (v(0) + v(1))) *
+             (1.0 / 2048.0);
+    else
+      return (3.0 * v(-2) - 25.0 * v(-1) + 150.0 * v(0) + 150.0 * v(1) - 25.0 * v(2) + 3.0 * v(3)) * (1.0 / 256.0);
+  };
+  const long long P = d.mplane;
+#pragma unroll
+  for (int e = tid; e < MT_X * MT_Y; e += MT_THREADS) {
+    const int ty = e / MT_X, tx = e % MT_X;
+    const int a = a0 + tx, b = b0 + ty;
+    if (a >= d.nx + GHOST || b >= d.ny + GHOST) continue;
+    const double *xe = &L.e[0][ty * EX + tx + LO], *ye = &L.e[1][ty * EX + tx + LO];
+    const double *xx = &L.x[0][(ty + LO) * MT_X + tx], *yx = &L.x[1][(ty + LO) * MT_X + tx];
+    double* m = M + (long long)(b + GHOST) * d.mpitch + (a + GHOST);
+    // Sec. 2.2 in two dimensions
+    const double j = xx[0] * ye[0] - xe[0] * yx[0];
+    m[0 * P] = ye[0];    // xi_x^
+    m[1 * P] = -xe[0];   // xi_y^
+    m[2 * P] = -yx[0];   // eta_x^
+    m[3 * P] = xx[0];    // eta_y^
+    m[4 * P] = j;        // J^{-1}
+    m[5 * P] = mid(ye, 1);
+    m[6 * P] = -mid(xe, 1);
+    m[7 * P] = -mid(yx, MT_X);
+    m[8 * P] = mid(xx, MT_X);
+    if (a >= 0 && a < d.nx && b >= 0 && b < d.ny && (!(j > 0.0) || !(j < 1.0e300))) atomicOr(status, ST_JACOBIAN);
+  }
+}
+
+// The blocks of a multi-block grid, whose extension crosses into neighbours, come
+// with their nodal metrics T[5][(ny+2B)(nx+2B)] on the band of width B.
 // Nodal and midpoint metrics on the stored band (width GHOST) plus the tag.
 __global__ void metrics_band_kernel(Dims d, int scheme, double ah, int B, const double* __restrict__ T,
                                     double* __restrict__ M, int* __restrict__ status) {
@@ -344,13 +438,17 @@ hipError_t launch_fill_u64(unsigned long long* p, long long n, hipStream_t st) {
 }
 
 hipError_t launch_metrics(const Dims& d, int scheme, double ah, const double* x, const double* y, double* M,
-                          double* T, int* status, hipStream_t st) {
-  const int B = metric_band(scheme);
-  dim3 b1(64, 4);
-  dim3 g1((d.nx + 2 * B + 63) / 64, (d.ny + 2 * B + 3) / 4);
-  hipLaunchKernelGGL(metrics_nodal_kernel, g1, b1, 0, st, d, metric_stencil(scheme, ah), B, x, y, T);
-  dim3 g2((d.nx + 2 * GHOST + 63) / 64, (d.ny + 2 * GHOST + 3) / 4);
-  hipLaunchKernelGGL(metrics_band_kernel, g2, b1, 0, st, d, scheme, ah, B, T, M, status);
+                          int* status, hipStream_t st) {
+  const MetricStencil ms = metric_stencil(scheme, ah);
+  int K = METRIC_REACH;
+  while (K > (scheme >= 4 ? 4 : 3) && ms.d[K - 1] == 0.0) --K;
+  const dim3 grid((d.nx + 2 * GHOST + MT_X - 1) / MT_X, (d.ny + 2 * GHOST + MT_Y - 1) / MT_Y);
+#define WIU_M2(k, eight)                                                                                     \
+  if (K == k && (scheme >= 4) == eight)                                                                      \
+    hipLaunchKernelGGL((metrics_kernel<k, eight>), grid, dim3(MT_THREADS), 0, st, d, ms, scheme, ah, x, y, M, \
+                       status);
+  WIU_M2(3, false) WIU_M2(4, false) WIU_M2(4, true) WIU_M2(5, true) WIU_M2(6, true) WIU_M2(7, true)
+#undef WIU_M2
   return hipGetLastError();
 }
 

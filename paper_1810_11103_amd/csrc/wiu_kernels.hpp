@@ -161,7 +161,7 @@ hipError_t launch_wave_max(const Dims& d, const double* U, const double* M, doub
                            unsigned long long* le, unsigned long long* cfl, int* status, hipStream_t st,
                            bool cleared = false);
 hipError_t launch_metrics(const Dims& d, int scheme, double ah, const double* x, const double* y, double* M,
-                          double* T, int* status, hipStream_t st);
+                          int* status, hipStream_t st);
 // Central metric operator of a scheme as an antisymmetric node stencil
 // sum_m d_m (g_{i+m} - g_{i-m}), m = 1..METRIC_REACH, and the width of the
 // nodal-metric band the midpoint interpolation needs.
