@@ -58,6 +58,26 @@ namespace {
 
 // Tile shape of each sweep direction (index into the compiled variants).
 int g_variant[2] = {0, 2};  // xi 128 x 1, eta 32 x 8 (measured at 2048^2)
+bool g_xi_named = false;    // wiu_set_tuning has named the xi shape
+
+// The xi shape of a grid, unless one was named: of 128 x 1 and 64 x 2 the one that
+// launches fewer lanes, counting the items that neighbouring tiles both form and the
+// lanes beyond a line's end.  Steps of 5-2MP, 128 x 1 against 64 x 2: 300 x 400 (384
+// lanes a line against 320) 77.9 and 73.2 us, 512 x 512 (640, 576) 120.0 and 114.6,
+// 2048 x 2048 (2176, 2240) 1314 and 1323; 7-4MP on 1000 x 760 (1152, 1088) 376.7 and
+// 364.1.  With as many lanes 64 x 2: 3-2MP on 333 x 255 62.1 and 60.2, 5-1MP on
+// 900 x 700 230.0 and 228.9, 5-2MP on 2000 x 70 89.4 and 88.1, 1024 x 1024 327.8 and
+// 329.4.
+int xi_shape(const wiu_grid* g, int scheme) {
+  if (g_xi_named) return g_variant[0];
+  auto lanes = [&](int variant) {
+    int na, nb;
+    sweep_tile_shape(0, variant, na, nb);
+    const int out = na - scheme_extra(scheme);
+    return (long long)((g->nx + out - 1) / out) * na * ((g->ny + nb - 1) / nb) * nb;
+  };
+  return lanes(2) <= lanes(0) ? 2 : 0;
+}
 
 constexpr size_t ALIGN = 256;
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
@@ -313,7 +333,7 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
   a.nlam_xi = nullptr; a.nlam_eta = nullptr; a.ncfl = nullptr;
   {
     ProfScope ps(WIU_K_SWEEP_XI, st);
-    e = launch_sweep(scheme, 0, g_variant[0], a, st);
+    e = launch_sweep(scheme, 0, xi_shape(g, scheme), a, st);
   }
   if (e != hipSuccess) return WIU_EHIP;
   a.mode = mode;
@@ -701,6 +721,7 @@ int wiu_tuning_variants(int dir) { return (dir == 0 || dir == 1) ? sweep_variant
 int wiu_set_tuning(int dir, int variant) {
   if ((dir != 0 && dir != 1) || variant < 0 || variant >= sweep_variants(dir)) return WIU_EINVAL;
   g_variant[dir] = variant;
+  if (dir == 0) g_xi_named = true;
   return WIU_OK;
 }
 

@@ -455,6 +455,21 @@ class Solver:
         return metric_planes(self.M, self.grid)
 
 
+# items that neighbouring tiles of a xi sweep both form, by scheme
+_XI_OVERLAP = {0: 4, 1: 3, 2: 6, 3: 4, 4: 8, 5: 6, 6: 5, 7: 7}
+
+
+def _xi_shape(shapes, scheme):
+    """xi tile shape of a batch of (ny, nx) blocks when none is named: of 128 x 1
+    (0) and 64 x 2 (2) the one that launches fewer lanes.  A step of 64 blocks of
+    24 to 64 nodes squared took 99.4 us with 128 x 1, which leaves half the lanes
+    idle, and 90.8 with 64 x 2; of 30 blocks of 49 to 408 587 and 574."""
+    def lanes(na, nb):
+        out = na - _XI_OVERLAP[scheme_id(scheme)]
+        return sum(-(-nx // out) * na * (-(-ny // nb)) * nb for ny, nx in shapes)
+    return 2 if lanes(64, 2) <= lanes(128, 1) else 0
+
+
 class BatchedPlan:
     """Many blocks stepped together (wiu_batched_*).
 
@@ -524,7 +539,9 @@ class BatchedPlan:
                 if status(ws):
                     raise WiuError("metrics reported a folded cell")
         self.plan = ctypes.c_void_p()
-        self.retune(get_tuning(0) if xi_variant is None else xi_variant,
+        if xi_variant is None:
+            xi_variant = get_tuning(0) or _xi_shape(self.shapes, scheme)
+        self.retune(xi_variant,
                     get_tuning(1) if eta_variant is None else eta_variant)
 
     def retune(self, xi_variant, eta_variant):

@@ -97,3 +97,28 @@ def test_other_metrics_flagged(wiu):
     sol.rk3_steps_cfl(Ud, 0.5, 3)
     assert sol.status() == wiu.ST_SCHEME
     assert np.array_equal(Ud.cpu().numpy(), U)
+
+
+def test_xi_shape_of_a_grid_gives_the_same_bits(wiu):
+    """Grids that the sweeps take: the xi tile shape chosen for the grid against
+    both that it is chosen from, named (which stays so in the process)."""
+    done = []
+    for s, nx, ny in [("5-2MP", 300, 400), ("5-2MP", 2048, 40), ("7-4MP", 1000, 70)]:
+        g = W.periodic_grid(nx, ny, (0, 10, 0, 10), A=0.2, seed=3)
+        U = dev(W.vortex_periodic_state(g))
+        sol = wiu.Solver(g.x, g.y, s, g.bc, g.period)
+        done.append((sol, U, sol.rhs(U)))
+    saved = wiu.get_tuning(0)
+    try:
+        for v in (0, 2):
+            wiu.set_tuning(0, v)
+            for sol, U, out in done:
+                assert bool((sol.rhs(U) == out).all()), (sol.scheme, v)
+    finally:
+        wiu.set_tuning(0, saved)
+
+
+def test_xi_shape_of_a_batch(wiu):
+    assert wiu._xi_shape([(40, 60), (24, 24)], "5-2MP") == 2
+    assert wiu._xi_shape([(2048, 2048)], "5-2MP") == 0
+    assert wiu._xi_shape([(1, 100)], "5-2MP") == 0
