@@ -782,6 +782,7 @@ struct S3Args {
   int weights;                     // WIU_WEIGHTS_*
   int split;                       // WIU_SPLIT_* of the leading midpoint flux
   double* Racc;                    // accumulated flux differences [5][np]
+  double* Reta;                    // those of the eta pass when it runs beside the zeta pass (or null)
   double* out;                     // dU/dt (mode 2) or the new stage state (mode 3)
   const double* U0;                // RK base state
   const double* dt;                // device time step
@@ -839,8 +840,7 @@ template <int SC, int DIR, int NA, int NB, bool OPT = false> struct Sweep3Lds {
 // it the sweep runs the paper's configuration and carries no code for them, and
 // PPM says whether the weights are mapped.
 template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
-__global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
-  __shared__ Sweep3Lds<SC, DIR, NA, NB, OPT> L;
+WIU_DEV void s3_sweep(const S3Args& a, int mode, long long tile, Sweep3Lds<SC, DIR, NA, NB, OPT>& L) {
   using R_ = Range<SC>;
   using LT = Sweep3Lds<SC, DIR, NA, NB, OPT>;
   constexpr int OUT = NA - R_::EXTRA, QL = R_::QL, NQ = LT::NQ, NT = NA * NB;
@@ -858,7 +858,6 @@ __global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
   // XCD-aware order: consecutive logical tiles share an XCD's L2; for eta
   // and zeta the line group (along i) varies fastest, so neighbouring tiles
   // read the same rows and pages of the k-planes
-  const long long tile = xcd_remap(blockIdx.x, gridDim.x);
   int seg, grp, cb;
   if (DIR == 0) {
     seg = (int)(tile % nseg);
@@ -1014,6 +1013,10 @@ __global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
     if (mode != 0) {
 #pragma unroll
       for (int c = 0; c < 5; ++c) xr[c] = a.Racc[c * d.np + t];
+      if (DIR == 0 && a.Reta) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) xr[c] += a.Reta[c * d.np + t];
+      }
     }
     if (mode >= 2) jv = a.M[9 * d.mplane + m3idx(d, p[0], p[1], p[2])];
     if (mode == 3 && a.ca != 0.0) {
@@ -1165,6 +1168,30 @@ __global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
   }
 }
 
+template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
+__global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
+  __shared__ Sweep3Lds<SC, DIR, NA, NB, OPT> L;
+  s3_sweep<SC, DIR, NA, NB, OPT, PPM>(a, mode, xcd_remap(blockIdx.x, gridDim.x), L);
+}
+
+// The zeta pass (the first tz tiles, into Racc) and the eta pass (into Reta) side by
+// side, both with mode 0.
+template <int SC, bool OPT, bool PPM>
+__global__ void __launch_bounds__(256) s3_pair_kernel(S3Args a, int tz) {
+  union Lds {
+    Sweep3Lds<SC, 1, 32, 8, OPT> e;
+    Sweep3Lds<SC, 2, 32, 8, OPT> z;
+  };
+  __shared__ Lds L;
+  const int b = blockIdx.x;
+  if (b < tz) {
+    s3_sweep<SC, 2, 32, 8, OPT, PPM>(a, 0, xcd_remap(b, tz), L.z);
+  } else {
+    a.Racc = a.Reta;
+    s3_sweep<SC, 1, 32, 8, OPT, PPM>(a, 0, xcd_remap(b - tz, gridDim.x - tz), L.e);
+  }
+}
+
 // Line maxima of the wave speeds in all three directions and the CFL
 // maximum.  One thread per (i, j) column walks a chunk of kc <= KC3 nodes along k
 // (the third grid dimension covers the chunks): zeta lines reduce in
@@ -1258,7 +1285,7 @@ Dims3 dims3(const wiu_grid3* g) {
 // Workspace: [status | line maxima, a ring of four sets (one per state) | dt | big area], the big area holding either the metric scratch
 // (inner derivatives, nodal band) or the stepping buffers (Racc, U1, U2).
 struct Ws3 {
-  size_t lam, dt, big, metric_dx, metric_t, metric_x, racc, u1, u2, total;
+  size_t lam, dt, big, metric_dx, metric_t, metric_x, racc, u1, u2, reta, total;
   long long nlam, set;  // words of a maxima set in use, and from one set to the next
 };
 
@@ -1281,6 +1308,15 @@ Box3 box3(const Dims3& d, int band, int reach) {
 // halo exceeds it.
 bool ext_in_metrics(const Dims3& d, const Box3& bx) { return 6 * bx.P <= NP3 * d.mplane; }
 
+// Grids whose zeta and eta passes run side by side, the eta differences in an array of
+// their own.  A pass of a small grid is as long as one wave's work, so one launch for
+// two saves its whole time: steps of 5-2MP on 40 x 36 x 33 nodes 122.2 -> 97.2 us,
+// 64^3 306.8 -> 289.9, 112^3 965 -> 945.  From 128^3 on (1543 and 1541, 160^3 2712 and
+// 2704) the passes fill the chip by themselves, and the array would be the
+// workspace's largest growth.
+constexpr long long PAIR3_NODES = 1LL << 21;
+bool pair3(const Dims3& d) { return d.np < PAIR3_NODES; }
+
 Ws3 ws3(const wiu_grid3* g) {
   const Dims3 d = dims3(g);
   Ws3 w;
@@ -1300,7 +1336,8 @@ Ws3 ws3(const wiu_grid3* g) {
   w.racc = w.big;
   w.u1 = w.racc + al3(5 * (size_t)d.np * 8);
   w.u2 = w.u1 + al3(5 * (size_t)d.np * 8);
-  const size_t step_end = w.u2 + al3(5 * (size_t)d.np * 8);
+  w.reta = w.u2 + al3(5 * (size_t)d.np * 8);
+  const size_t step_end = w.reta + (pair3(d) ? al3(5 * (size_t)d.np * 8) : 0);
   const size_t met_end = w.metric_x + (ext_in_metrics(d, bx) ? 0 : al3(6 * (size_t)bx.P * 8));
   w.total = step_end > met_end ? step_end : met_end;
   return w;
@@ -1335,56 +1372,72 @@ dim3 box_grid(const Box3& b) { return dim3((unsigned)(((b.w[0] * b.w[1] + 255) /
 
 // Tile shapes: xi 64 items x 4 lines (lanes along the line, one line per
 // wave), eta and zeta 32 items x 8 lines (lanes across the lines, along i).
+template <int SC, int DIR, int NA, int NB> unsigned tiles3(const Dims3& d) {
+  constexpr int OUT = NA - Range<SC>::EXTRA;
+  const int nac = DIR == 0 ? d.n[1] : d.n[0];
+  const int nb = DIR == 2 ? d.n[1] : d.n[2];
+  return (unsigned)((long long)((d.n[DIR] + OUT - 1) / OUT) * ((nac + NB - 1) / NB) * nb);
+}
+
 template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
 hipError_t launch_sweep3_t(const S3Args& a, int mode, hipStream_t st) {
-  constexpr int OUT = NA - Range<SC>::EXTRA;
-  const int n = a.d.n[DIR];
-  const int nac = DIR == 0 ? a.d.n[1] : a.d.n[0];
-  const int nb = DIR == 2 ? a.d.n[1] : a.d.n[2];
-  const long long tiles = (long long)((n + OUT - 1) / OUT) * ((nac + NB - 1) / NB) * nb;
+  const unsigned tiles = tiles3<SC, DIR, NA, NB>(a.d);
   const dim3 block = DIR == 0 ? dim3(NA, NB) : dim3(NB, NA);
   void* h = prof_open(WIU_K_SWEEP3, st);
-  hipLaunchKernelGGL((s3_sweep_kernel<SC, DIR, NA, NB, OPT, PPM>), dim3((unsigned)tiles), block, 0, st, a, mode);
+  hipLaunchKernelGGL((s3_sweep_kernel<SC, DIR, NA, NB, OPT, PPM>), dim3(tiles), block, 0, st, a, mode);
   prof_close(h);
   return hipGetLastError();
 }
 
+// The three passes: zeta, eta, then xi with mode `last`, which reads what they left.
 template <int SC, bool OPT, bool PPM>
-hipError_t launch_pass3_o(const S3Args& a, int D, int mode, hipStream_t st) {
-  if (D == 0) return launch_sweep3_t<SC, 0, 64, 4, OPT, PPM>(a, mode, st);
-  if (D == 1) return launch_sweep3_t<SC, 1, 32, 8, OPT, PPM>(a, mode, st);
-  return launch_sweep3_t<SC, 2, 32, 8, OPT, PPM>(a, mode, st);
+hipError_t launch_passes3_o(const S3Args& a, int last, hipStream_t st) {
+  hipError_t e;
+  if (a.Reta) {
+    const unsigned tz = tiles3<SC, 2, 32, 8>(a.d), te = tiles3<SC, 1, 32, 8>(a.d);
+    void* h = prof_open(WIU_K_SWEEP3, st);
+    hipLaunchKernelGGL((s3_pair_kernel<SC, OPT, PPM>), dim3(tz + te), dim3(8, 32), 0, st, a, (int)tz);
+    prof_close(h);
+    e = hipGetLastError();
+  } else {
+    e = launch_sweep3_t<SC, 2, 32, 8, OPT, PPM>(a, 0, st);
+    if (e == hipSuccess) e = launch_sweep3_t<SC, 1, 32, 8, OPT, PPM>(a, 1, st);
+  }
+  return e == hipSuccess ? launch_sweep3_t<SC, 0, 64, 4, OPT, PPM>(a, last, st) : e;
 }
 
 // the options kernels only when an option is in use
 template <int SC>
-hipError_t launch_pass3(const S3Args& a, int D, int mode, hipStream_t st) {
-  if (a.vars != 0 || a.ah != 1.0 || a.weights != 0 || a.split != 0) return launch_pass3_o<SC, true, true>(a, D, mode, st);
-  return a.ppm ? launch_pass3_o<SC, false, true>(a, D, mode, st) : launch_pass3_o<SC, false, false>(a, D, mode, st);
+hipError_t launch_passes3(const S3Args& a, int last, hipStream_t st) {
+  if (a.vars != 0 || a.ah != 1.0 || a.weights != 0 || a.split != 0) return launch_passes3_o<SC, true, true>(a, last, st);
+  return a.ppm ? launch_passes3_o<SC, false, true>(a, last, st) : launch_passes3_o<SC, false, false>(a, last, st);
 }
 
-hipError_t pass3(int scheme, const S3Args& a, int D, int mode, hipStream_t st) {
+hipError_t passes3(int scheme, const S3Args& a, int last, hipStream_t st) {
   switch (scheme) {
-    case 0: return launch_pass3<0>(a, D, mode, st);
-    case 1: return launch_pass3<1>(a, D, mode, st);
-    case 2: return launch_pass3<2>(a, D, mode, st);
-    case 3: return launch_pass3<3>(a, D, mode, st);
-    case 4: return launch_pass3<4>(a, D, mode, st);
-    case 5: return launch_pass3<5>(a, D, mode, st);
-    case 6: return launch_pass3<6>(a, D, mode, st);
-    case 7: return launch_pass3<7>(a, D, mode, st);
+    case 0: return launch_passes3<0>(a, last, st);
+    case 1: return launch_passes3<1>(a, last, st);
+    case 2: return launch_passes3<2>(a, last, st);
+    case 3: return launch_passes3<3>(a, last, st);
+    case 4: return launch_passes3<4>(a, last, st);
+    case 5: return launch_passes3<5>(a, last, st);
+    case 6: return launch_passes3<6>(a, last, st);
+    case 7: return launch_passes3<7>(a, last, st);
     default: return hipErrorInvalidValue;
   }
 }
 
 // Line maxima and the CFL maximum of U into a cleared set.  Each thread walks
-// KC3 nodes along k, fewer while that leaves the chip without blocks: on
-// 40 x 36 x 33 nodes 16 in a row left 27 blocks and took 34 us.
+// KC3 nodes along k, fewer while that leaves the chip without blocks; more blocks
+// are more atomics on the same lines.  Steps with at least 64, 128, 256 and 1024
+// blocks: 40 x 36 x 33 nodes 88.8, 90.5, 97.5 and 97.4 us, 64^3 259, 254, 257 and 290,
+// 47 x 180 x 98 612, 614, 613 and 642.  On 40 x 36 x 33 nodes 27 blocks took 34 us for
+// this pass alone.
 hipError_t maxima3(const Dims3& d, const double* U, const double* M, double gam, unsigned long long* lam, int* status,
                    hipStream_t st) {
   const long long cols = (long long)((d.n[0] + 63) / 64) * ((d.n[1] + 3) / 4);
   int kc = KC3;
-  while (kc > 1 && cols * ((d.n[2] + kc - 1) / kc) < 1024) kc >>= 1;
+  while (kc > 1 && cols * ((d.n[2] + kc - 1) / kc) < 128) kc >>= 1;
   hipLaunchKernelGGL(w3_max_kernel, dim3((d.n[0] + 63) / 64, (d.n[1] + 3) / 4, (d.n[2] + kc - 1) / kc), dim3(256), 0,
                      st, d, kc, U, M, gam, lam, status);
   return hipGetLastError();
@@ -1415,6 +1468,7 @@ static int rk3_3d(const wiu_grid3* g, int scheme, const wiu_params* p, double* U
   a.d = d; a.M = M; a.lam = (unsigned long long*)(base + w.lam);
   a.gamma = p->gamma; a.alpha = p->alpha_lf; a.eps = p->eps; a.ppm = p->ppm;
   a.Racc = (double*)(base + w.racc);
+  a.Reta = pair3(d) ? (double*)(base + w.reta) : nullptr;
   a.U0 = U; a.status = (int*)base;
   sides3(g, a);
   options3(p, a);
@@ -1442,12 +1496,9 @@ static int rk3_3d(const wiu_grid3* g, int scheme, const wiu_params* p, double* U
       a.U = src[s]; a.out = dst[s]; a.ca = ca[s]; a.cb = cb[s];
       a.lam = set(0);  // the maxima of U, U1, U2
       unsigned long long* next = s < 2 || step + 1 < nsteps ? set(1) : nullptr;
-      for (int q = 0; q < 3; ++q) {  // zeta, eta, then xi, which writes the stage state
-        const int D = 2 - q;
-        a.nlam = D == 0 ? next : nullptr;
-        a.ncfl = D == 0 && s == 2 && next ? next + w.nlam : nullptr;
-        if (pass3(scheme, a, D, q == 0 ? 0 : (q == 1 ? 1 : 3), st) != hipSuccess) return WIU_EHIP;
-      }
+      a.nlam = next;
+      a.ncfl = s == 2 && next ? next + w.nlam : nullptr;
+      if (passes3(scheme, a, 3, st) != hipSuccess) return WIU_EHIP;
     }
   }
   return WIU_OK;
@@ -1511,15 +1562,14 @@ int wiu3_rhs(const wiu_grid3* g, int scheme, const wiu_params* p, const double* 
   a.ncfl = nullptr;
   a.d = d; a.U = U; a.M = M; a.lam = (unsigned long long*)(base + w.lam);
   a.gamma = p->gamma; a.alpha = p->alpha_lf; a.eps = p->eps; a.ppm = p->ppm;
-  a.Racc = (double*)(base + w.racc); a.out = dUdt;
+  a.Racc = (double*)(base + w.racc);
+  a.Reta = pair3(d) ? (double*)(base + w.reta) : nullptr; a.out = dUdt;
   sides3(g, a);
   options3(p, a);
   a.U0 = nullptr; a.dt = nullptr; a.ca = 0.0; a.cb = 1.0; a.status = (int*)base;
   if (launch_fill_u64((unsigned long long*)a.lam, w.nlam, st) != hipSuccess) return WIU_EHIP;
   if (maxima3(d, U, M, p->gamma, (unsigned long long*)a.lam, a.status, st) != hipSuccess) return WIU_EHIP;
-  for (int q = 0; q < 3; ++q)  // zeta, eta, then xi, which writes dU/dt
-    if (pass3(scheme, a, 2 - q, q == 0 ? 0 : (q == 1 ? 1 : 2), st) != hipSuccess) return WIU_EHIP;
-  return WIU_OK;
+  return rc3(passes3(scheme, a, 2, st));
 }
 
 int wiu3_cfl_dt(const wiu_grid3* g, const wiu_params* p, const double* U, const double* M, double cfl, double* dt,
