@@ -442,7 +442,8 @@ int wiu3_rk3_steps_cfl(const wiu_grid3* g, int scheme, const wiu_params* p, doub
 /* Tile shapes of the two sweep kernels (dir 0 = xi, 1 = eta).  Several
  * shapes are compiled; the choice is process-wide and affects speed only,
  * never results.  wiu_tuning_variants() returns how many shapes a direction
- * has, wiu_set_tuning() selects one (WIU_EINVAL when out of range). */
+ * has, wiu_set_tuning() selects one (WIU_EINVAL when out of range).  Until a xi
+ * shape is selected, sweeps of a single grid take shape 0 or 2, by the grid. */
 int wiu_tuning_variants(int dir);
 int wiu_set_tuning(int dir, int variant);
 int wiu_get_tuning(int dir);

@@ -3,15 +3,15 @@
 // symmetric conservative form (Eq. 2.4) with each scheme's central operator,
 // Jacobian by Eq. 2.5, the characteristic projection of Sec. 3.4 with five
 // eigenvectors, the WENOIU midpoint fluxes and upwind-biased difference of
-// every scheme, TVD-RK3.  The paper's configuration only (characteristic
-// variables, Lax-Friedrichs split, alpha = 1, Jiang-Shu weights).
+// every scheme, TVD-RK3; the scheme options in kernels of their own.
 //
 // A direction pass is one LDS-tiled sweep (states staged once, one item per
 // lane, item records in LDS, the flux difference and the stage update in the
 // same kernel), with lanes along i wherever global memory is touched so
 // loads and stores coalesce whatever the line direction.  The passes run
 // zeta, eta, xi: the xi pass, whose lines are contiguous in memory, writes
-// dU/dt or the RK stage (and, in stages 1 and 2, the next stage's maxima).
+// dU/dt or the RK stage (and the next state's maxima).  On grids that do not fill
+// the chip zeta and eta are one launch.
 #include "wenoiu.h"
 
 #include "wiu_kernels.hpp"
@@ -834,7 +834,7 @@ template <int SC, int DIR, int NA, int NB, bool OPT = false> struct Sweep3Lds {
 // (nodal flux at k and both side fluxes at k + 1/2), then the first OUT
 // lanes of each line form H_{i+1/2} - H_{i-1/2} and, by `mode`: 0 Racc = R;
 // 1 Racc += R; 2 dU/dt = -(Racc + R)/J^{-1}; 3 the RK stage
-// U_out = ca U0 + cb (U + dt dU/dt).  Four block-wide barriers on every path
+// U_out = ca U0 + cb (U + dt dU/dt); the xi pass adds Reta to Racc when that is set.  Four block-wide barriers on every path
 // (five in an xi pass that accumulates the next stage's maxima).
 // OPT: compiled with the scheme options (a.vars, a.ah, a.weights); without
 // it the sweep runs the paper's configuration and carries no code for them, and
