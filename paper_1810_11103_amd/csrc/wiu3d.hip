@@ -1169,7 +1169,7 @@ WIU_DEV void s3_sweep(const S3Args& a, int mode, long long tile, Sweep3Lds<SC, D
 }
 
 template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
-__global__ void __launch_bounds__(NA * NB) s3_sweep_kernel(S3Args a, int mode) {
+__global__ void __launch_bounds__(NA * NB, NA == 30 ? 4 : 1) s3_sweep_kernel(S3Args a, int mode) {
   __shared__ Sweep3Lds<SC, DIR, NA, NB, OPT> L;
   s3_sweep<SC, DIR, NA, NB, OPT, PPM>(a, mode, xcd_remap(blockIdx.x, gridDim.x), L);
 }
@@ -1389,6 +1389,21 @@ hipError_t launch_sweep3_t(const S3Args& a, int mode, hipStream_t st) {
   return hipGetLastError();
 }
 
+// An eta or zeta pass of its own.  Tiles of 30 x 8 items need 40.0 KB of LDS, so four
+// workgroups share a CU where of 32 x 8 (42.6 KB) three do; they are taken where a line
+// has no more segments for it.  Steps with 32 x 8 against 30 x 8: 5-2MP on 256^3 (10
+// segments with either) 11.31 and 11.00-11.10 ms, 3-1MP on 200 x 200 x 180 4.39 and
+// 4.15-4.17; with more segments 5-2MP on 160^3 (6 against 7) 2.77 and 2.82-2.87.  The
+// seventh-order and options kernels hold more LDS or registers than that.
+template <int SC, int DIR, bool OPT, bool PPM>
+hipError_t launch_across3(const S3Args& a, int mode, hipStream_t st) {
+  if constexpr (!OPT && Range<SC>::QL == 2) {
+    auto segments = [&](int na) { const int out = na - Range<SC>::EXTRA; return (a.d.n[DIR] + out - 1) / out; };
+    if (segments(30) == segments(32)) return launch_sweep3_t<SC, DIR, 30, 8, OPT, PPM>(a, mode, st);
+  }
+  return launch_sweep3_t<SC, DIR, 32, 8, OPT, PPM>(a, mode, st);
+}
+
 // The three passes: zeta, eta, then xi with mode `last`, which reads what they left.
 template <int SC, bool OPT, bool PPM>
 hipError_t launch_passes3_o(const S3Args& a, int last, hipStream_t st) {
@@ -1400,8 +1415,8 @@ hipError_t launch_passes3_o(const S3Args& a, int last, hipStream_t st) {
     prof_close(h);
     e = hipGetLastError();
   } else {
-    e = launch_sweep3_t<SC, 2, 32, 8, OPT, PPM>(a, 0, st);
-    if (e == hipSuccess) e = launch_sweep3_t<SC, 1, 32, 8, OPT, PPM>(a, 1, st);
+    e = launch_across3<SC, 2, OPT, PPM>(a, 0, st);
+    if (e == hipSuccess) e = launch_across3<SC, 1, OPT, PPM>(a, 1, st);
   }
   return e == hipSuccess ? launch_sweep3_t<SC, 0, 64, 4, OPT, PPM>(a, last, st) : e;
 }

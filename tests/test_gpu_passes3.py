@@ -1,5 +1,6 @@
 """3-D passes on both sides of the grid size from which the zeta and eta passes run
-one after the other instead of side by side (2^21 nodes): a grid that repeats a
+one after the other instead of side by side (2^21 nodes), with tiles of 30 items where
+a line has as many segments of them as of 32, else of 32: a grid that repeats a
 smaller one ten times along k has the smaller one's residual in every period, and a
 step's increments.  Bar 1e-11 of each component's maximum: the repeated coordinates
 carry 2^-53 of ten periods, 1.4e-14 of a cell's size, and the residual is a difference
@@ -15,6 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("s,n,kw", [("5-2MP", (130, 126, 13), {}), ("3-1MP", (64, 257, 13), {}),
+                                    ("5-2MP", (128, 140, 13), {}), ("5-1MP", (66, 262, 13), {}),
                                     ("7-2MP", (128, 128, 13), {"vars": "primitive"})])
 def test_repeated_grid(s, n, kw):
     import torch
