@@ -118,10 +118,14 @@ struct Coord3 {
 // copies are the nodal values); the inner box is K wider, the coordinates K
 // wider again.  The boundary rule is thus applied once per position, and the
 // stencils behind it are plain accesses at constant strides.  150 x 131 x 117
-// periodic, WENOIU5-2MP: 651 us (ext 46, inner 151, nodal 257, band 197),
+// periodic, WENOIU5-2MP: 641 us (traced: ext 42, inner 176, nodal 241, band 199),
 // bound by the L2 traffic of the stencils and, in the nodal kernel, by LDS
 // reads and issue alike; 4818 us (inner 643, nodal 3961, band 214) when every
-// tap applied the rule to both of its ends.
+// tap applied the rule to both of its ends.  The same nodes with bounded ends, whose
+// boxes hold as many positions beyond the grid as in it: 1011 us (76, 300, 467, 191).
+// Coordinates relative to a tile's first node, one word each, took 895 there and 640
+// on the periodic grid, but left metrics off by up to 1.6e-14 of their value where
+// the spacing is small against the tile's extent (now 8e-16).
 // Scratch arrays are stored row by row, the components of a row next to each
 // other ([k][j][component][i]): a stencil tap then touches one stretch of
 // memory for all its components instead of one page for each.
@@ -168,40 +172,34 @@ WIU_DEV bool b3_node(const Box3& b, int& i, int& j, int& k) {
 // Tile of the derivative kernels: 16 x 8 x 4 nodes.
 constexpr int T3_X = 16, T3_Y = 8, T3_Z = 4;
 
-// Whether the positions within `reach` of (i, j, k) are nodes of the grid
-// (their lo parts are exactly zero there and are not read).
-WIU_DEV bool inside3(const Dims3& d, int i, int j, int k, int reach) {
-  return i >= reach && i < d.n[0] - reach && j >= reach && j < d.n[1] - reach && k >= reach && k < d.n[2] - reach;
+// Whether (i, j, k) is a node of the grid.
+WIU_DEV bool inside3(const Dims3& d, int i, int j, int k) {
+  return i >= 0 && i < d.n[0] && j >= 0 && j < d.n[1] && k >= 0 && k < d.n[2];
 }
 
 // Coordinates on the box, as the unevaluated sum hi + lo of node coordinate
 // and offset (exact): components 0..2 hi, 3..5 lo.  A difference of two
 // positions is (hi1 - hi0) + (lo1 - lo0), which keeps its digits across a
-// seam.  Only tiles that reach beyond an end read lo parts, none of a node
-// 2 K + T3_X or more from every end, where they are not written.
-__global__ void __launch_bounds__(256) m3_ext_kernel(Dims3 d, Box3 bx, int K, Coord3 X, double* __restrict__ XE) {
+// seam and where the spacing is small against the coordinates of the nodes
+// around.  The lo part of a node of the grid is zero, neither written nor read.
+__global__ void __launch_bounds__(256) m3_ext_kernel(Dims3 d, Box3 bx, Coord3 X, double* __restrict__ XE) {
   int p[3];
   if (!b3_node(bx, p[0], p[1], p[2])) return;
   double* xe = XE + b3idx(bx, 6, p[0], p[1], p[2]);
-  const bool in = inside3(d, p[0], p[1], p[2], 0), deep = inside3(d, p[0], p[1], p[2], 2 * K + T3_X);
-  const long long o = u3idx(d, p[0], p[1], p[2]);
-  double hi[3], lo[3] = {0.0, 0.0, 0.0};
-  if (in) {
+  if (inside3(d, p[0], p[1], p[2])) {
+    const long long o = u3idx(d, p[0], p[1], p[2]);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) hi[c] = X.x[c][o];
-  } else {
-    const Pos3 r = c3_pos(d, p);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double b, f;
-      c3_at(d, X.x[c], c, r, b, f);
-      two_sum(b, f, hi[c], lo[c]);
-    }
+    for (int c = 0; c < 3; ++c) xe[c * bx.pitch] = X.x[c][o];
+    return;
   }
+  const Pos3 r = c3_pos(d, p);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    xe[c * bx.pitch] = hi[c];
-    if (!deep) xe[(3 + c) * bx.pitch] = lo[c];
+    double b, f, hi, lo;
+    c3_at(d, X.x[c], c, r, b, f);
+    two_sum(b, f, hi, lo);
+    xe[c * bx.pitch] = hi;
+    xe[(3 + c) * bx.pitch] = lo;
   }
 }
 
@@ -271,9 +269,8 @@ template <int O, int K> WIU_DEV int tile3_slot(const Tile3& t) {
 
 // What a lane stages for one direction, held in registers between its loads
 // (all issued together, before the work on the direction before) and its
-// LDS stores: coordinates and, with G, three of the inner derivatives.  A
-// coordinate is the node coordinate itself in tiles that read nodes of the
-// grid only, else it is relative to the tile's first node.
+// LDS stores: the hi parts of the coordinates and, with G, three of the inner
+// derivatives.
 template <int O, int K, bool X, bool G> struct Lane3 {
   static constexpr int N = (Stage3<O, K>::A * Stage3<O, K>::C + 511) / 512;
   double x[N][3], g[N][3];
@@ -294,20 +291,6 @@ template <int O, int K, bool X, bool G> struct Lane3 {
         for (int c = 0; c < 3; ++c) g[n][c] = v[(3 * inner + c) * bi.pitch];
       }
     }
-    if constexpr (X) {
-      if (!t.in) {
-        const double* v0 = XE + b3idx(bx, 6, t.q[0], t.q[1], t.q[2]);
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-          int p[3];
-          tile3_pos<O, K>(t, min((int)threadIdx.x + 512 * n, Stage3<O, K>::A * Stage3<O, K>::C - 1), p);
-          const double* v = XE + b3idx(bx, 6, p[0], p[1], p[2]);
-#pragma unroll
-          for (int c = 0; c < 3; ++c)
-            x[n][c] = (x[n][c] - v0[c * bx.pitch]) + (v[(3 + c) * bx.pitch] - v0[(3 + c) * bx.pitch]);
-        }
-      }
-    }
   }
   WIU_DEV void store(const Tile3& t, double* L) const {
     constexpr int NP = stage3_slots<K>();
@@ -326,16 +309,65 @@ template <int O, int K, bool X, bool G> struct Lane3 {
   }
 };
 
-// Derivatives along O of the three staged coordinates.
+// The lo parts of the positions m along O from this lane's node (a lane beyond the
+// box takes the box's last).  They are zero but beyond the grid, where they are
+// read from memory: few waves of the tiles at its ends do, and staging them too
+// would take half as much LDS again.
+template <int O> struct Lo3 {
+  int a, n, pitch;
+  bool out;  // the whole line lies beyond the grid
+  long long st;
+  const double* p;
+  WIU_DEV Lo3(const Dims3& d, const Tile3& t, const Box3& bx, const double* __restrict__ XE) : out(false) {
+    const int q[3] = {min(t.q[0] + t.x, t.e[0] - 1), min(t.q[1] + t.y, t.e[1] - 1), min(t.q[2] + t.z, t.e[2] - 1)};
+    long long s3[3];
+    b3strides(bx, 6, s3);
+    a = q[O]; n = d.n[O]; pitch = bx.pitch; st = s3[O];
+    p = XE + b3idx(bx, 6, q[0], q[1], q[2]) + 3 * pitch;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) out = out || (c != O && (q[c] < 0 || q[c] >= d.n[c]));
+  }
+  // whether any of the positions 0 .. K (sd 0) or -K .. 0 (sd 1) lies beyond the grid
+  WIU_DEV bool beyond(int sd, int K) const { return out || a < (sd ? K : 0) || a + (sd ? 0 : K) >= n; }
+  WIU_DEV void at(int m, double v[3]) const {
+    const bool o = out || a + m < 0 || a + m >= n;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c] = o ? p[m * st + c * pitch] : 0.0;
+  }
+};
+
+// Derivatives along O of the three coordinates, whose hi parts are staged, added to s.
 template <int O, int K> WIU_DEV void inner3_dir(const Tile3& t, const MetricStencil& ms, const double* L, double s[3]) {
   constexpr int NP = stage3_slots<K>(), S = Stage3<O, K>::S;
   const double* v = L + tile3_slot<O, K>(t);
-#pragma unroll
-  for (int c = 0; c < 3; ++c) s[c] = 0.0;
 #pragma unroll 1
   for (int m = 1; m <= K; ++m)
 #pragma unroll
     for (int c = 0; c < 3; ++c) s[c] += ms.d[m - 1] * (v[c * NP + m * S] - v[c * NP - m * S]);
+}
+// Those of the lo parts, in s (as differences from the node's: zero on a line where
+// they are all the same).
+template <int O, int K>
+WIU_DEV void inner3_lo(const Dims3& d, const Tile3& t, const Box3& bx, const double* __restrict__ XE,
+                       const MetricStencil& ms, double s[3]) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) s[c] = 0.0;
+  if (t.in) return;
+  const Lo3<O> lo(d, t, bx, XE);
+  if (!lo.beyond(0, K) && !lo.beyond(1, K)) return;
+  double own[3];
+  lo.at(0, own);
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd) {
+    if (!lo.beyond(sd, K)) continue;
+    double v[K][3];
+#pragma unroll
+    for (int m = 1; m <= K; ++m) lo.at(sd ? -m : m, v[m - 1]);
+#pragma unroll
+    for (int m = 1; m <= K; ++m)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) s[c] = fma(sd ? -ms.d[m - 1] : ms.d[m - 1], v[m - 1][c] - own[c], s[c]);
+  }
 }
 
 // Inner derivatives D_a x_c (a, c = 0..2) on their box: component 3a + c.
@@ -348,6 +380,9 @@ __global__ void __launch_bounds__(512) m3_inner_kernel(Dims3 d, MetricStencil ms
   Lane3<0, K, true, false> l0;
   Lane3<1, K, true, false> l1;
   Lane3<2, K, true, false> l2;
+  inner3_lo<0, K>(d, t, bx, XE, ms, s);
+  inner3_lo<1, K>(d, t, bx, XE, ms, s + 3);
+  inner3_lo<2, K>(d, t, bx, XE, ms, s + 6);
   l0.load(t, bx, XE, bi, Dx, 0);
   l0.store(t, L);
   __syncthreads();
@@ -371,9 +406,18 @@ __global__ void __launch_bounds__(512) m3_inner_kernel(Dims3 d, MetricStencil ms
 
 // Outer direction O of the nodal metrics: D_O(r x g_i) of the staged inner
 // direction i, added to n^_{O+2} (i = O+1) or taken from n^_{O+1} (i = O+2).
+template <int O, int K, int H> WIU_DEV void nodal3_add(const double r[3], const double* u, double nh[9]) {
+  constexpr int NP = stage3_slots<K>(), to = (O + 2 - H) % 3;
+#pragma unroll
+  for (int l = 0; l < 3; ++l) {
+    const int p = (l + 1) % 3, q = (l + 2) % 3;
+    nh[3 * to + l] = fma(r[p], u[(3 + q) * NP], nh[3 * to + l]);
+    nh[3 * to + l] = fma(-r[q], u[(3 + p) * NP], nh[3 * to + l]);
+  }
+}
 template <int O, int K, int H>
 WIU_DEV void nodal3_dir(const Tile3& t, const MetricStencil& ms, const double* L, double nh[9]) {
-  constexpr int NP = stage3_slots<K>(), S = Stage3<O, K>::S, to = (O + 2 - H) % 3;
+  constexpr int NP = stage3_slots<K>(), S = Stage3<O, K>::S;
   const double* v = L + tile3_slot<O, K>(t);
   const double x0[3] = {v[0], v[NP], v[2 * NP]};
 #pragma unroll 1
@@ -385,13 +429,44 @@ WIU_DEV void nodal3_dir(const Tile3& t, const MetricStencil& ms, const double* L
       double r[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) r[c] = w * (u[c * NP] - x0[c]);
-#pragma unroll
-      for (int l = 0; l < 3; ++l) {
-        const int p = (l + 1) % 3, q = (l + 2) % 3;
-        nh[3 * to + l] = fma(r[p], u[(3 + q) * NP], nh[3 * to + l]);
-        nh[3 * to + l] = fma(-r[q], u[(3 + p) * NP], nh[3 * to + l]);
-      }
+      nodal3_add<O, K, H>(r, u, nh);
     }
+}
+// What the lo parts of the coordinates add to it: those of a lane's taps in
+// registers, where both inner directions of O use them.
+template <int O, int K> struct Taps3 {
+  double own[3], lo[2][K][3];  // of the node; of the positions m (0) and -m (1)
+  bool far[2];
+  WIU_DEV Taps3(const Dims3& d, const Tile3& t, const Box3& bx, const double* __restrict__ XE) {
+    far[0] = far[1] = false;
+    if (t.in) return;
+    const Lo3<O> l(d, t, bx, XE);
+    far[0] = l.beyond(0, K);
+    far[1] = l.beyond(1, K);
+    if (far[0] || far[1]) l.at(0, own);
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd) {
+      if (!far[sd]) continue;
+#pragma unroll
+      for (int m = 1; m <= K; ++m) l.at(sd ? -m : m, lo[sd][m - 1]);
+    }
+  }
+};
+template <int O, int K, int H>
+WIU_DEV void nodal3_lo(const Tile3& t, const MetricStencil& ms, const double* L, const Taps3<O, K>& x, double nh[9]) {
+  const double* v = L + tile3_slot<O, K>(t);
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd) {
+    if (!x.far[sd]) continue;
+#pragma unroll
+    for (int m = 1; m <= K; ++m) {
+      const double w = (sd != H) ? -ms.d[m - 1] : ms.d[m - 1];
+      double r[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) r[c] = w * (x.lo[sd][m - 1][c] - x.own[c]);
+      nodal3_add<O, K, H>(r, v + (sd ? -m : m) * Stage3<O, K>::S, nh);
+    }
+  }
 }
 
 // Nodal metrics (Eq. 2.4) and J^{-1} (Eq. 2.5) on their box, ten components.
@@ -418,31 +493,46 @@ __global__ void __launch_bounds__(512) m3_nodal_kernel(Dims3 d, MetricStencil ms
   a0.load(t, bx, XE, bi, Dx, 1);
   a0.store(t, L);
   __syncthreads();
-  b0.load(t, bx, XE, bi, Dx, 2);
-  nodal3_dir<0, K, 0>(t, ms, L, nh);
-  __syncthreads();
-  b0.store(t, L);
-  __syncthreads();
+  {
+    b0.load(t, bx, XE, bi, Dx, 2);
+    nodal3_dir<0, K, 0>(t, ms, L, nh);
+    const Taps3<0, K> lo(d, t, bx, XE);
+    nodal3_lo<0, K, 0>(t, ms, L, lo, nh);
+    __syncthreads();
+    b0.store(t, L);
+    __syncthreads();
+    nodal3_lo<0, K, 1>(t, ms, L, lo, nh);
+  }
   a1.load(t, bx, XE, bi, Dx, 2);
   nodal3_dir<0, K, 1>(t, ms, L, nh);
   __syncthreads();
   a1.store(t, L);
   __syncthreads();
-  b1.load(t, bx, XE, bi, Dx, 0);
-  nodal3_dir<1, K, 0>(t, ms, L, nh);
-  __syncthreads();
-  b1.store(t, L);
-  __syncthreads();
+  {
+    b1.load(t, bx, XE, bi, Dx, 0);
+    nodal3_dir<1, K, 0>(t, ms, L, nh);
+    const Taps3<1, K> lo(d, t, bx, XE);
+    nodal3_lo<1, K, 0>(t, ms, L, lo, nh);
+    __syncthreads();
+    b1.store(t, L);
+    __syncthreads();
+    nodal3_lo<1, K, 1>(t, ms, L, lo, nh);
+  }
   a2.load(t, bx, XE, bi, Dx, 0);
   nodal3_dir<1, K, 1>(t, ms, L, nh);
   __syncthreads();
   a2.store(t, L);
   __syncthreads();
-  b2.load(t, bx, XE, bi, Dx, 1);
-  nodal3_dir<2, K, 0>(t, ms, L, nh);
-  __syncthreads();
-  b2.store(t, L);
-  __syncthreads();
+  {
+    b2.load(t, bx, XE, bi, Dx, 1);
+    nodal3_dir<2, K, 0>(t, ms, L, nh);
+    const Taps3<2, K> lo(d, t, bx, XE);
+    nodal3_lo<2, K, 0>(t, ms, L, lo, nh);
+    __syncthreads();
+    b2.store(t, L);
+    __syncthreads();
+    nodal3_lo<2, K, 1>(t, ms, L, lo, nh);
+  }
   nodal3_dir<2, K, 1>(t, ms, L, nh);
   const int i = t.q[0] + t.x, j = t.q[1] + t.y, k = t.q[2] + t.z;
   if (i >= t.e[0] || j >= t.e[1] || k >= t.e[2]) return;
@@ -522,7 +612,7 @@ __global__ void __launch_bounds__(256) m3_band_kernel(Dims3 d, int scheme, Box3 
                    3.0 * v[q[6]]) * (1.0 / 256.0);
     }
   }
-  if (inside3(d, p[0], p[1], p[2], 0)) {
+  if (inside3(d, p[0], p[1], p[2])) {
     const double j = J6 ? M[9 * d.mplane + t] : v0[9 * W];
     if (!(j > 0.0) || !(j < 1.0e300)) atomicOr(status, ST_JACOBIAN);
   }
@@ -1550,7 +1640,7 @@ int wiu3_metrics(const wiu_grid3* g, int scheme, int jform, const wiu_params* p,
   const Coord3 X{{x, y, z}};
   Box3 bm;
   for (int q = 0; q < 3; ++q) bm.w[q] = d.n[q] + 2 * GHOST;
-  hipLaunchKernelGGL(m3_ext_kernel, box_grid(bx), dim3(256), 0, st, d, bx, K, X, XE);
+  hipLaunchKernelGGL(m3_ext_kernel, box_grid(bx), dim3(256), 0, st, d, bx, X, XE);
 #define WIU_M3(k)                                                                                      \
   case k:                                                                                              \
     hipLaunchKernelGGL(m3_inner_kernel<k>, tile_grid(bi), dim3(512), 0, st, d, ms, bi, bx, XE, Dx);    \

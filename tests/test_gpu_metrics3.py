@@ -47,3 +47,35 @@ def test_metrics_tile_edges(orc, wiu, s, n, kind, jform):
         scale = max(np.abs(ref[p]).max() for p in planes)
         for p in planes:
             assert np.abs(M[p] - ref[p]).max() <= 1e-13 * scale, p
+
+
+@pytest.mark.parametrize("s,K", [("3-1MP", 3), ("5-2MP", 4), ("7-6MP", 7)])
+def test_metrics_of_a_clustered_grid(orc, wiu, s, K):
+    """Coordinates through zero with a spacing that grows by up to 1.4 a node, so that
+    neighbours differ by little against the nodes around: every metric to its own
+    magnitude, in the tiles at the ends too.  On a tensor-product grid Eq. 2.4 gives
+    products of one-dimensional derivatives, formed here in extended precision.  Bar:
+    the roundings of two derivatives of K taps and of the 4 K terms of the nodal
+    sums, each at most 2^-53 of the terms, whose magnitudes add up to at most twice
+    their sum."""
+    print("metrics3 clustered", s, file=sys.stderr, flush=True)
+    L = np.longdouble
+    n = (41, 37, 30)
+    X = [np.sinh(7 * np.linspace(-1, 1, m)) / np.sinh(7.0) for m in n]
+    z, y, x = np.meshgrid(X[2], X[1], X[0], indexing="ij")
+    M = wiu.Solver3(x, y, z, s, ("transmissive",) * 3, (0.0,) * 3).planes().cpu().numpy()[:, 4:-4, 4:-4, 4:-4]
+    c = {"3-1MP": [L(557) / 768, -L(25) / 192, L(3) / 256],
+         "5-2MP": [L(487) / 640, -L(103) / 640, L(41) / 1920, -L(1) / 1280],
+         "7-6MP": [L(5983587) / 7340032, -L(57115) / 262144, L(153455) / 3145728, -L(1411) / 196608,
+                   L(10039) / 15728640, -L(89) / 1835008, L(15) / 7340032]}[s]
+    D = []
+    for a in X:
+        a = a.astype(L)
+        m = np.arange(1, K + 1).astype(L)
+        e = np.concatenate([a[0] + m[::-1] * (a[0] - a[1]), a, a[-1] + m * (a[-1] - a[-2])])
+        D.append(sum(c[q - 1] * (e[K + q:K + q + len(a)] - e[K - q:K - q + len(a)]) for q in range(1, K + 1)))
+    dz, dy, dx = np.meshgrid(D[2], D[1], D[0], indexing="ij")
+    bar = 2 * (2 * (K + 2) + 4 * K) * 2.0 ** -53
+    for p, ref in ((0, dy * dz), (4, dz * dx), (8, dx * dy), (9, dx * dy * dz)):
+        err = np.abs((M[p] - ref) / ref).max()
+        assert err <= bar, (p, float(err), bar)
