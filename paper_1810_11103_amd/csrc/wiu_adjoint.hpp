@@ -11,8 +11,8 @@ namespace wiu {
 
 // ---------------------------------------------------------------------------
 // WENO r = 3 (inputs a, b, d, e around the zero centre) -- see weno5, whose
-// scaled quantities are used throughout: with p_k the candidates times 8 c_k, E_k
-// = 4 (eps + IS_k) and D_k = E_k^2, P_k the products of the other two D, S_P =
+// quantities are used throughout: with p_k the candidates times 8 c_k, E_k =
+// eps + IS_k and D_k = E_k^2, P_k the products of the other two D, S_P =
 // sum c_k P_k, r = 1/S_P, x_k = 16 P_k r - 1, g_k = 1 + K_k x_k^3 (in units of
 // C_k), S = sum c_k g_k, N = sum g_k p_k, the value is out = N / (8 S).  Returns
 // out; v[] enters as the inputs and leaves as out's derivatives by them.
@@ -25,12 +25,11 @@ template <bool PPM> WIU_DEV double weno5_grad(double v[4], double eps) {
   const double b10 = 10.0 * b, d30 = 30.0 * d;
   const double p[3] = {fma(3.0, a, -b10), d30 - b10, fma(-5.0, e, d30)};
   const double t[3] = {fma(-2.0, b, a), b + d, fma(-2.0, d, e)};
-  const double s[3] = {fma(-4.0, b, a), b - d, fma(-4.0, d, e)};
-  const double eps4 = 4.0 * eps;
+  const double u[3] = {fma(-0.5, a, t[0]), fma(0.5, t[1], -d), fma(-0.5, e, t[2])};
   double E[3], D[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    E[k] = fma(13.0 / 3.0, t[k] * t[k], fma(s[k], s[k], eps4));
+    E[k] = fma(13.0 / 12.0, t[k] * t[k], fma(u[k], u[k], eps));
     D[k] = E[k] * E[k];
   }
   const double P[3] = {D[1] * D[2], D[0] * D[2], D[0] * D[1]};
@@ -67,12 +66,12 @@ template <bool PPM> WIU_DEV double weno5_grad(double v[4], double eps) {
   for (int k = 0; k < 3; ++k) Pb[k] = fma(q16, z[k], c[k] * SPb);
   const double Db[3] = {fma(Pb[1], D[2], Pb[2] * D[1]), fma(Pb[0], D[2], Pb[2] * D[0]),
                         fma(Pb[0], D[1], Pb[1] * D[0])};
-  double tb[3], sb[3];
+  double tb[3], sb[3];  // by t, and by s = 2 u (a - 4 b, b - d, e - 4 d)
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const double f = 4.0 * (E[k] * Db[k]);
+    const double f = E[k] * Db[k];
     tb[k] = (13.0 / 3.0 * f) * t[k];
-    sb[k] = f * s[k];
+    sb[k] = (2.0 * f) * u[k];
   }
   const double p01 = pb[0] + pb[1], p12 = pb[1] + pb[2];
   v[0] = fma(3.0, pb[0], tb[0] + sb[0]);
@@ -89,12 +88,11 @@ template <bool PPM> WIU_DEV double weno3_grad(double v[3], double eps) {
   const double a = v[0], b = v[1], d = v[2];
   const double KL[2] = {WIU_M2L0 * 0.25, WIU_M2L1 * 0.75};
   const double KH[2] = {WIU_M2H0 * 0.25, WIU_M2H1 * 0.75};
-  const double t[2] = {fma(-2.0, b, a), b + d}, s[2] = {fma(-4.0, b, a), b - d};
-  const double eps4 = 4.0 * eps;
+  const double t[2] = {fma(-2.0, b, a), b + d}, u[2] = {fma(-0.5, a, t[0]), fma(0.5, t[1], -d)};
   double E[2], D[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    E[k] = fma(13.0 / 3.0, t[k] * t[k], fma(s[k], s[k], eps4));
+    E[k] = fma(13.0 / 12.0, t[k] * t[k], fma(u[k], u[k], eps));
     D[k] = E[k] * E[k];
   }
   const double r = rcp_w(fma(3.0, D[0], D[1])), r4 = 4.0 * r;
@@ -118,9 +116,10 @@ template <bool PPM> WIU_DEV double weno3_grad(double v[3], double eps) {
   const double z0 = (Sb - Nb * b) * gx[0], z1 = 3.0 * ((Nb * d + Sb) * gx[1]);
   const double T = fma(x[0], z0, z0) + fma(x[1], z1, z1);
   const double q = 2.0 * r, q4 = 4.0 * q, SPb = -(q * T);
-  // P_0 = D_1, P_1 = D_0 with weights 1 and 3 in S_P; dD = 2 E dE
-  const double f1 = 4.0 * (E[1] * fma(q4, z0, SPb)), f0 = 4.0 * (E[0] * fma(q4, z1, 3.0 * SPb));
-  const double tb0 = (13.0 / 3.0 * f0) * t[0], sb0 = f0 * s[0], tb1 = (13.0 / 3.0 * f1) * t[1], sb1 = f1 * s[1];
+  // P_0 = D_1, P_1 = D_0 with weights 1 and 3 in S_P; dD = 2 E dE; s = 2 u
+  const double f1 = E[1] * fma(q4, z0, SPb), f0 = E[0] * fma(q4, z1, 3.0 * SPb);
+  const double tb0 = (13.0 / 3.0 * f0) * t[0], sb0 = (2.0 * f0) * u[0];
+  const double tb1 = (13.0 / 3.0 * f1) * t[1], sb1 = (2.0 * f1) * u[1];
   v[0] = tb0 + sb0;
   v[1] = fma(-2.0, tb0, fma(-4.0, sb0, tb1 + sb1)) - Nb * g[0];
   v[2] = (tb1 - sb1) + Nb * g1;

@@ -223,10 +223,11 @@ template <int R> constexpr double WSCALE = R == 2 ? 2.0 : (R == 3 ? 8.0 : 16.0);
 
 // r = 3: left-biased value at k+1/2 from v_{k-2}, v_{k-1}, v_k = 0, v_{k+1},
 // v_{k+2} = (a, b, 0, d, e).  Candidates from Table 1 (b_{k,l}), linear
-// weights (1, 10, 5)/16, Jiang-Shu indicators (Eq. 3.22), four times over,
-//   4 IS = 13/3 t^2 + s^2
-// (t0 = a - 2b, s0 = a - 4b; t1 = b + d, s1 = b - d; t2 = e - 2d, s2 = e - 4d;
-// the factor cancels in the weights), weights alpha_k / sum alpha with alpha_k =
+// weights (1, 10, 5)/16, Jiang-Shu indicators (Eq. 3.22)
+//   IS = 13/12 t^2 + u^2
+// (t0 = a - 2b, u0 = t0 - a/2; t1 = b + d, u1 = t1/2 - d; t2 = e - 2d, u2 = t2 - e/2;
+// not a multiple of them: the weights take their fourth powers, of which a factor
+// would cost range), weights alpha_k / sum alpha with alpha_k =
 // C_k / (eps + IS_k)^2 formed with one reciprocal (w_k = c_k P_k / sum_m c_m P_m,
 // P_k = prod_{l != k} (eps + IS_l)^2), mapping Eq. 3.23 and re-normalisation.
 // With w_k, the C_k multiples and the candidates' eighths formed one by one an
@@ -240,11 +241,10 @@ WIU_DEV double weno5(double a, double b, double d, double e, double eps, int ppm
   const double b10 = 10.0 * b, d30 = 30.0 * d;
   const double p0 = fma(3.0, a, -b10), p1 = d30 - b10, p2 = fma(-5.0, e, d30);
   const double t0 = fma(-2.0, b, a), t1 = b + d, t2 = fma(-2.0, d, e);
-  const double s0 = fma(-4.0, b, a), s1 = b - d, s2 = fma(-4.0, d, e);
-  const double eps4 = 4.0 * eps;
-  double D0 = fma(13.0 / 3.0, t0 * t0, fma(s0, s0, eps4));
-  double D1 = fma(13.0 / 3.0, t1 * t1, fma(s1, s1, eps4));
-  double D2 = fma(13.0 / 3.0, t2 * t2, fma(s2, s2, eps4));
+  const double u0 = fma(-0.5, a, t0), u1 = fma(0.5, t1, -d), u2 = fma(-0.5, e, t2);
+  double D0 = fma(13.0 / 12.0, t0 * t0, fma(u0, u0, eps));
+  double D1 = fma(13.0 / 12.0, t1 * t1, fma(u1, u1, eps));
+  double D2 = fma(13.0 / 12.0, t2 * t2, fma(u2, u2, eps));
   if constexpr (ZOK) {
     if (ppm == 2) {
       // tau = |IS_0 - IS_2|; q_k = tau / (eps + IS_k) from one reciprocal
@@ -277,10 +277,9 @@ template <bool ZOK = false>
 WIU_DEV double weno3(double a, double b, double d, double eps, int ppm) {
   // the first two r = 3 indicators, in the form of weno5
   const double t0 = fma(-2.0, b, a), t1 = b + d;
-  const double s0 = fma(-4.0, b, a), s1 = b - d;
-  const double eps4 = 4.0 * eps;
-  double D0 = fma(13.0 / 3.0, t0 * t0, fma(s0, s0, eps4));
-  double D1 = fma(13.0 / 3.0, t1 * t1, fma(s1, s1, eps4));
+  const double u0 = fma(-0.5, a, t0), u1 = fma(0.5, t1, -d);
+  double D0 = fma(13.0 / 12.0, t0 * t0, fma(u0, u0, eps));
+  double D1 = fma(13.0 / 12.0, t1 * t1, fma(u1, u1, eps));
   if constexpr (ZOK) {
     if (ppm == 2) {  // WENO-Z, tau = |IS_0 - IS_1|
       const double R = rcp_w(D0 * D1), tau = fabs(D0 - D1);
@@ -322,8 +321,9 @@ WIU_DEV double weno3(double a, double b, double d, double eps, int ppm) {
 // where y = c1 + c3/4, c2 and c3 are fixed differences of the stencil values.
 // Formed nine times over from 3 y, 2 c2 and 6 c3, whose differences have a unit
 // coefficient each: 9 IS = (3y)^2 + 39/4 (2 c2)^2 + 781/80 (6 c3)^2.
-// Weights as in weno5 (products of the squared denominators, one
-// reciprocal), mapping map4, re-normalisation.
+// Weights as in weno5 (products of the squared denominators, one reciprocal),
+// mapping map4, re-normalisation.  The products carry 9^6 < 2^20, which is taken out
+// of each, so that states overflow no sooner than with IS itself.
 template <bool ZOK = false>
 WIU_DEV double weno7(double a, double b, double c, double e, double f, double g, double eps, int ppm) {
   const double p0 = fma(-5.0, a, fma(21.0, b, -35.0 * c));
@@ -341,8 +341,9 @@ WIU_DEV double weno7(double a, double b, double c, double e, double f, double g,
   double D3 = is(fma(-4.5, f, fma(9.0, e, g)), fma(4.0, f, fma(-5.0, e, -g)), fma(3.0, e - f, g));
   if constexpr (ZOK) {
     if (ppm == 2) {  // WENO-Z, tau = |IS_0 + 3 IS_1 - 3 IS_2 - IS_3|
-      const double P01 = D0 * D1, P23 = D2 * D3, R = rcp_w(P01 * P23);
-      const double tau = fabs(fma(3.0, D1 - D2, D0 - D3));
+      // (9^4 < 2^14 taken out of the product of all four)
+      const double P01 = D0 * (0x1p-7 * D1), P23 = D2 * (0x1p-7 * D3), R = rcp_w(P01 * P23);
+      const double tau = 0x1p-7 * fabs(fma(3.0, D1 - D2, D0 - D3));
       const double q0 = tau * (D1 * P23 * R), q1 = tau * (D0 * P23 * R);
       const double q2 = tau * (D3 * P01 * R), q3 = tau * (D2 * P01 * R);
       const double a0 = fma(q0, q0, 1.0), a1 = 21.0 * fma(q1, q1, 1.0);
@@ -351,7 +352,7 @@ WIU_DEV double weno7(double a, double b, double c, double e, double f, double g,
     }
   }
   D0 *= D0; D1 *= D1; D2 *= D2; D3 *= D3;
-  const double P01 = D0 * D1, P23 = D2 * D3;
+  const double P01 = D0 * (0x1p-20 * D1), P23 = D2 * (0x1p-20 * D3);
   const double P0 = D1 * P23, P1 = D0 * P23, P2 = D3 * P01, P3 = D2 * P01;
   const double r = rcp_w(fma(21.0, P1, P0) + fma(35.0, P2, 7.0 * P3));
   double g0, g1, g2, g3;  // g_0 / C, g_k / C_k
