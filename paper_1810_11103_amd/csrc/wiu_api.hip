@@ -192,7 +192,7 @@ struct Ws {
   unsigned long long *lx, *le, *cfl;
   unsigned long long *lx2, *le2;  // a second set: maxima of an RK stage state, from the previous stage
   // sets in all, contiguous from lx and `set` words apart: four, or in
-  // wiu_rk3_step_noalloc three with stage tiles and two with the sweeps
+  // wiu_rk3_step_noalloc three on small grids and two on others
   int nsets;
   long long set;
   double *rxi, *u1, *u2;
@@ -273,7 +273,8 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? WIU_OK : WIU_EHIP; }
 struct Maxima {
   const unsigned long long *lx_in = nullptr, *le_in = nullptr;
   unsigned long long *nlx = nullptr, *nle = nullptr;
-  unsigned long long* ncfl = nullptr;  // with nlx: per eta line CFL maxima of the new state (nlx + nx + ny + 1)
+  // with nlx: CFL maxima of the new state (nlx + nx + ny + 1), per eta line or in cfl_words words
+  unsigned long long* ncfl = nullptr;
   unsigned long long* wm = nullptr;  // target of the separate pass (lx[ny], le[nx], cfl[1]); default the workspace's
   bool cleared = false;              // nlx (and ncfl) are zero already
   // stage tiles only (StageArgs): the step size from CFL maxima, a set to
@@ -285,7 +286,10 @@ struct Maxima {
   unsigned long long* clear = nullptr;
 };
 
-bool stage_tiles(const wiu_grid* g) { return use_stage_tiles((long long)g->nx * g->ny); }
+bool stage_tiles(const wiu_grid* g, int scheme) { return use_stage_tiles(scheme, g->nx, g->ny); }
+
+// CFL maxima that a step's last stage leaves: one per eta line, or the stage tiles' words.
+int cfl_words(const wiu_grid* g, bool tiles) { return tiles && g->nx > CFL_SLOTS ? CFL_SLOTS : g->nx; }
 
 // Words of a maxima set with its per-line CFL maxima.
 long long set_words(const wiu_grid* g) { return 2LL * g->nx + g->ny + 1; }
@@ -316,7 +320,7 @@ int residual(const wiu_grid* g, int scheme, const wiu_params* p, const double* U
   // one set is contiguous: lam_xi[ny], lam_eta[nx], cfl[1] (and the per-line
   // CFL maxima[nx] when they are accumulated too)
   const long long next_len = (long long)d.nx + d.ny + 1 + (mx.ncfl ? d.nx : 0);
-  if (stage_tiles(g)) {
+  if (stage_tiles(g, scheme)) {
     StageArgs t;
     t.s = a;
     t.s.mode = mode; t.s.Rxi = nullptr; t.s.out = out; t.s.U0 = U0; t.s.dt = dt; t.s.ca = ca; t.s.cb = cb;
@@ -367,7 +371,7 @@ int rk3_stages(const wiu_grid* g, int scheme, const wiu_params* p, double* U, co
                double* U2, const Ws& w, hipStream_t st, double cfl = 0.0, unsigned long long* rec = nullptr,
                bool inplace = false) {
   const long long ns = (long long)g->nx + g->ny + 1;
-  const bool tiles = stage_tiles(g), three = rec || w.nsets > 2;
+  const bool tiles = stage_tiles(g, scheme), three = rec || w.nsets > 2;
   unsigned long long* m0 = rec ? rec : w.lx;                                      // maxima of U
   unsigned long long* mA = rec ? rec + ns : w.lx2;                                // of U1
   unsigned long long* mB = rec ? rec + 2 * ns : (three ? w.lx + 2 * w.set : w.lx);  // of U2
@@ -405,10 +409,12 @@ constexpr int NOALLOC_MAX_DEVICES = 64;
 std::mutex g_noalloc_mu;
 void* g_noalloc_ptr[NOALLOC_MAX_DEVICES] = {};
 
-// Layout in the scratch: two sets of line maxima (three with stage tiles),
-// then the two stage buffers (P / U1 and P / U2, see rk3_stages).
+// Layout in the scratch: two sets of line maxima, three where some scheme takes
+// stage tiles (small grids, far below the limit), then the two stage buffers (P / U1
+// and P / U2, see rk3_stages).
 struct NoallocLayout {
-  size_t lam, lam2, a, b, total;  // a third set follows lam2 with stage tiles (small grids, far below the limit)
+  int nsets;
+  size_t lam, lam2, a, b, total;
 };
 NoallocLayout noalloc_layout(const wiu_grid* g) {
   NoallocLayout L;
@@ -416,7 +422,8 @@ NoallocLayout noalloc_layout(const wiu_grid* g) {
   const size_t lam = align_up(((size_t)g->nx + g->ny + 1) * 8);
   L.lam = 0;
   L.lam2 = lam;
-  L.a = (stage_tiles(g) ? 3 : 2) * lam;
+  L.nsets = stage_tiles(g, WIU_3_1MP) ? 3 : 2;
+  L.a = L.nsets * lam;
   L.b = L.a + align_up(4 * np * 8);
   L.total = L.b + align_up(4 * np * 8);
   return L;
@@ -534,7 +541,7 @@ int wiu_rk3_steps_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double
   // sets are cleared together at first; later a step's three are cleared by the
   // launch that forms its step size, or with stage tiles by the stage before
   // the one that accumulates them (whose last reader was the stage before).
-  const bool tiles = stage_tiles(g);
+  const bool tiles = stage_tiles(g, scheme);
   int c = 0;
   auto set = [&](int k) { return w.lx + ((c + k) & 3) * w.set; };
   if (launch_fill_u64(w.lx, 4 * w.set, st) != hipSuccess) return WIU_EHIP;
@@ -549,7 +556,7 @@ int wiu_rk3_steps_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double
   for (int s = 0; s < nsteps; ++s) {
     double* dt = dt_dev + s;
     const unsigned long long* cflw = s == 0 ? set(0) + nxy : set(0) + nxy + 1;
-    const int ncflw = s == 0 ? 1 : g->nx;
+    const int ncflw = s == 0 ? 1 : cfl_words(g, tiles);
     if (!tiles && launch_step_begin(cflw, ncflw, cfl, dt, s == 0 ? nullptr : w.lx, w.set, 4, c, st) != hipSuccess)
       return WIU_EHIP;
     for (int q = 0; q < 3; ++q, c = (c + 1) & 3) {
@@ -588,7 +595,7 @@ int wiu_rk3_step_noalloc(const wiu_grid* g, int scheme, const wiu_params* p, dou
   w.cfl = w.le + g->nx;
   w.lx2 = (unsigned long long*)(b + L.lam2);
   w.le2 = w.lx2 + g->ny;
-  w.nsets = stage_tiles(g) ? 3 : 2;
+  w.nsets = L.nsets;
   w.set = (long long)((L.lam2 - L.lam) / 8);
   double* A = (double*)(b + L.a);
   double* B = (double*)(b + L.b);

@@ -66,15 +66,15 @@ struct StageArgs {
   unsigned long long* clear;         // when set, `nclear` words to zero (the maxima of the stage after next)
   long long nclear;
 };
+// Stage tiles accumulate the CFL maxima of a state (SweepArgs::ncfl) not per eta line but in
+// this many words (nx if that is less), which every workgroup of the next step's first
+// stage reduces for itself: one load a lane, however long the lines.  With a word a
+// line, each of the 8192 workgroups of a row of 65536 nodes reduced 65536 words: four
+// steps of 5-2MP 2020 us, 1259 so.
+constexpr int CFL_SLOTS = 64;
 
-// Grids of at most this many nodes step with the stage tiles, larger ones with
-// the sweeps.  RK3 steps with stage tiles / sweeps, microseconds: 5-2MP 27.5 /
-// 53.1 on 67 x 59 nodes, 39.1 / 60.4 on 195 x 187, 60.9 / 65.4 on 259 x 251,
-// 105 / 88 on 387 x 379; 7-4MP 83 / 85 and 3-1MP 50 / 59 on 259 x 251.  Below
-// the line the sweeps' time is the latency of their launches, above it the
-// tiles pay for their halos.
-constexpr long long STAGE_NODES = 1 << 16;
-bool use_stage_tiles(long long nodes);
+// Whether a grid steps with the stage tiles instead of the sweeps (wiu_stage_kernels.hip).
+bool use_stage_tiles(int scheme, int nx, int ny);
 hipError_t launch_stage(int scheme, const StageArgs& a, hipStream_t st);
 
 // One block of a batched multi-block problem (device table entry).  The

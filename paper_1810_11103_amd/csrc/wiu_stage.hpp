@@ -365,8 +365,8 @@ WIU_DEV void stage_tile(const StageArgs& a, int bx, int by, int wg, int nwg, Sta
   if (ti == 0 && act) atomicMax(&s.nlam_xi[jj], (unsigned long long)__double_as_longlong(sx));
   if (col) atomicMax(&s.nlam_eta[ii], (unsigned long long)__double_as_longlong(se));
   if (s.ncfl) {
-    for (int off = TX; off < 64; off <<= 1) cf = fmax(cf, __shfl_xor(cf, off, 64));
-    if (col) atomicMax(&s.ncfl[ii], (unsigned long long)__double_as_longlong(cf));
+    for (int off = 1; off < 64; off <<= 1) cf = fmax(cf, __shfl_xor(cf, off, 64));
+    if ((tid & 63) == 0) atomicMax(&s.ncfl[wg % min(d.nx, CFL_SLOTS)], (unsigned long long)__double_as_longlong(cf));
   }
 }
 

@@ -53,6 +53,22 @@ hipError_t launch_stage(int scheme, const StageArgs& a, hipStream_t st) {
   }
 }
 
-bool use_stage_tiles(long long nodes) { return nodes <= STAGE_NODES; }
+// Grids of at most 65536 nodes step with the stage tiles, larger ones with the sweeps.
+// RK3 steps with stage tiles / sweeps, microseconds: 5-2MP 27.5 / 53.1 on 67 x 59
+// nodes, 39.1 / 60.4 on 195 x 187, 60.9 / 65.4 on 259 x 251, 105 / 88 on 387 x 379;
+// 7-4MP 83 / 85 and 3-1MP 50 / 59 on 259 x 251.  Below the line the sweeps' time is
+// the latency of their launches, above it the tiles pay for their halos.  Beyond
+// 1400 tiles (65536 nodes fill 1024) lines that leave the tiles' last row or column
+// empty count: 7281 x 9, 1822 tiles, 94.4 / 88.5, 7-6MP 141 / 120, but 5000 x 13, 1250
+// tiles, 73.5 / 78.3 and 101 / 97.  On grids of a few rows or columns the sweep
+// across them is as empty: 32768 x 2, 4096 tiles, 174 / 189 and 239 / 236, 3 x 20000
+// 152 / 279; 65536 x 1 300 / 312, but 7-6MP, whose tiles' halo is nearly twice as wide,
+// 420 / 355, 24576 x 1 173 / 163 and 8192 x 1, 1024 tiles, 82 / 93.
+bool use_stage_tiles(int scheme, int nx, int ny) {
+  if ((long long)nx * ny > 65536) return false;
+  const int tiles = ((nx + ST_X - 1) / ST_X) * ((ny + ST_Y - 1) / ST_Y);
+  if (ny == 1 && scheme >= 4) return tiles <= 1024;
+  return tiles <= 1400 || ny <= ST_Y || nx <= 3 * ST_X;
+}
 
 }  // namespace wiu
