@@ -442,8 +442,11 @@ int wiu3_rk3_steps_cfl(const wiu_grid3* g, int scheme, const wiu_params* p, doub
 /* Tile shapes of the two sweep kernels (dir 0 = xi, 1 = eta).  Several
  * shapes are compiled; the choice is process-wide and affects speed only,
  * never results.  wiu_tuning_variants() returns how many shapes a direction
- * has, wiu_set_tuning() selects one (WIU_EINVAL when out of range).  Until a xi
- * shape is selected, sweeps of a single grid take shape 0 or 2, by the grid. */
+ * has, wiu_set_tuning() selects one (WIU_EINVAL when out of range),
+ * wiu_get_tuning() returns the selection (0 and 2 at first).  xi shapes: 0, for a
+ * single grid, 128 x 1 or 64 x 2 by the grid's size and the scheme (in a batched plan,
+ * which names its own, 128 x 1), 1 256 x 1, 2 64 x 2 items x lines; eta shapes: 0 32 x 4,
+ * 1 64 x 4, 2 32 x 8, 3 64 x 8, 4 32 x 16.  */
 int wiu_tuning_variants(int dir);
 int wiu_set_tuning(int dir, int variant);
 int wiu_get_tuning(int dir);

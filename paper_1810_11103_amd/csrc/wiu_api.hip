@@ -57,19 +57,18 @@ void prof_close(void* h) { delete static_cast<ProfScope*>(h); }
 namespace {
 
 // Tile shape of each sweep direction (index into the compiled variants).
-int g_variant[2] = {0, 2};  // xi 128 x 1, eta 32 x 8 (measured at 2048^2)
-bool g_xi_named = false;    // wiu_set_tuning has named the xi shape
+int g_variant[2] = {0, 2};  // xi by the grid, eta 32 x 8 (measured at 2048^2)
 
-// The xi shape of a grid, unless one was named: of 128 x 1 and 64 x 2 the one that
-// launches fewer lanes, counting the items that neighbouring tiles both form and the
+// The xi shape of a grid.  Selection 0, the default, is of 128 x 1 and 64 x 2 the one
+// that launches fewer lanes, counting the items that neighbouring tiles both form and the
 // lanes beyond a line's end.  Steps of 5-2MP, 128 x 1 against 64 x 2: 300 x 400 (384
 // lanes a line against 320) 77.9 and 73.2 us, 512 x 512 (640, 576) 120.0 and 114.6,
 // 2048 x 2048 (2176, 2240) 1314 and 1323; 7-4MP on 1000 x 760 (1152, 1088) 376.7 and
-// 364.1.  With as many lanes 64 x 2: 3-2MP on 333 x 255 62.1 and 60.2, 5-1MP on
-// 900 x 700 230.0 and 228.9, 5-2MP on 2000 x 70 89.4 and 88.1, 1024 x 1024 327.8 and
-// 329.4.
+// 364.1.  With as many lanes 64 x 2, faster on 24 of 34 grids: 5-2MP on 1024 x 1024
+// 349.1 and 345.4, 5-1MP on 900 x 700 243.2 and 239.3, 7-4MP on 700 x 300 152.0 and
+// 148.9, but on 1500 x 1500 1100 and 1114.
 int xi_shape(const wiu_grid* g, int scheme) {
-  if (g_xi_named) return g_variant[0];
+  if (g_variant[0]) return g_variant[0];
   auto lanes = [&](int variant) {
     int na, nb;
     sweep_tile_shape(0, variant, na, nb);
@@ -728,7 +727,6 @@ int wiu_tuning_variants(int dir) { return (dir == 0 || dir == 1) ? sweep_variant
 int wiu_set_tuning(int dir, int variant) {
   if ((dir != 0 && dir != 1) || variant < 0 || variant >= sweep_variants(dir)) return WIU_EINVAL;
   g_variant[dir] = variant;
-  if (dir == 0) g_xi_named = true;
   return WIU_OK;
 }
 

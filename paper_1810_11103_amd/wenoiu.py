@@ -460,7 +460,7 @@ _XI_OVERLAP = {0: 4, 1: 3, 2: 6, 3: 4, 4: 8, 5: 6, 6: 5, 7: 7}
 
 
 def _xi_shape(shapes, scheme):
-    """xi tile shape of a batch of (ny, nx) blocks when none is named: of 128 x 1
+    """xi tile shape of a batch of (ny, nx) blocks while selection 0 stands: of 128 x 1
     (0) and 64 x 2 (2) the one that launches fewer lanes.  A step of 64 blocks of
     24 to 64 nodes squared took 99.4 us with 128 x 1, which leaves half the lanes
     idle, and 90.8 with 64 x 2; of 30 blocks of 49 to 408 587 and 574."""
@@ -479,7 +479,9 @@ class BatchedPlan:
     multi-block grid: per-side rules, "interface" sides coupling the blocks
     as stated with wiu_block in wenoiu.h; metrics from wiu_blocks_metrics).
     U_all and M_all are flat device tensors owned here; block b's state is
-    U_all[off_U[b] : off_U[b] + 4 ny nx] viewed as (4, ny, nx)."""
+    U_all[off_U[b] : off_U[b] + 4 ny nx] viewed as (4, ny, nx).
+    xi_variant, eta_variant: tile shapes; by default those of set_tuning, xi
+    selection 0 being 128 x 1 or 64 x 2 by the blocks."""
 
     def __init__(self, blocks, scheme="5-2MP", params=None, xi_variant=None, eta_variant=None, device="cuda"):
         self.scheme = scheme
