@@ -446,10 +446,14 @@ int wiu3_rk3_steps_cfl(const wiu_grid3* g, int scheme, const wiu_params* p, doub
  * wiu_get_tuning() returns the selection (0 and 2 at first).  xi shapes: 0, for a
  * single grid, 128 x 1 or 64 x 2 by the grid's size and the scheme (in a batched plan,
  * which names its own, 128 x 1), 1 256 x 1, 2 64 x 2 items x lines; eta shapes: 0 32 x 4,
- * 1 64 x 4, 2 32 x 8, 3 64 x 8, 4 32 x 16.  */
+ * 1 64 x 4, 2 32 x 8, 3 64 x 8, 4 32 x 16.  Small grids (at most 65536 nodes) step with
+ * tiles of both directions instead of the sweeps and take no selection:
+ * wiu_tuning_applies() returns 1 if the sweeps serve a single grid, 0 if those tiles
+ * do (WIU_EINVAL for an invalid grid or scheme). */
 int wiu_tuning_variants(int dir);
 int wiu_set_tuning(int dir, int variant);
 int wiu_get_tuning(int dir);
+int wiu_tuning_applies(const wiu_grid* g, int scheme);
 
 /* Kernel timing for benchmarks.  While enabled, every launch of the
  * library's kernels is bracketed by HIP events recorded on its launch stream.

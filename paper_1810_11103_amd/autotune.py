@@ -78,7 +78,12 @@ def tune_batched(plan, reps=3, cache=DEFAULT_CACHE, force=False):
 
 
 def tune_single(solver, U, reps=3, cache=DEFAULT_CACHE, force=False):
-    """Pick the process-wide tile shapes for one grid (rhs timings)."""
+    """Pick the process-wide tile shapes for one grid (rhs timings).  A grid that
+    the sweeps do not serve leaves them, and the cache, as they are."""
+    if not wenoiu.tuning_applies(solver.grid, solver.scheme):
+        out = torch.empty_like(U)
+        return {"variant": [wenoiu.get_tuning(0), wenoiu.get_tuning(1)],
+                "ms": _time(lambda: solver.rhs(U, out), reps), "all_ms": {}}
     key = _key("single", solver.scheme, solver.grid.nx * solver.grid.ny)
     table = _load(cache) if cache else {}
     if not force and key in table:

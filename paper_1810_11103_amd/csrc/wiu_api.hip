@@ -730,6 +730,11 @@ int wiu_set_tuning(int dir, int variant) {
   return WIU_OK;
 }
 
+int wiu_tuning_applies(const wiu_grid* g, int scheme) {
+  if (!grid_ok(g) || !scheme_ok(scheme)) return WIU_EINVAL;
+  return stage_tiles(g, scheme) ? 0 : 1;
+}
+
 int wiu_get_tuning(int dir) { return (dir == 0 || dir == 1) ? g_variant[dir] : WIU_EINVAL; }
 
 int wiu_profile_enable(int on) {

@@ -23,6 +23,7 @@ EXPORTS = [
     "wiu_metrics_size", "wiu_workspace_bytes", "wiu_workspace_init", "wiu_metrics", "wiu_set_metrics_tag",
     "wiu_line_eigenvalues", "wiu_rhs", "wiu_cfl_dt", "wiu_rk3_step", "wiu_status", "wiu_strerror",
     "wiu_profile_enable", "wiu_profile_read", "wiu_tuning_variants", "wiu_set_tuning", "wiu_get_tuning",
+    "wiu_tuning_applies",
     "wiu_batched_plan", "wiu_batched_info", "wiu_batched_set_dt", "wiu_batched_cfl_dt", "wiu_batched_get_dt",
     "wiu_batched_rk3_step", "wiu_batched_status", "wiu_plan_destroy", "wiu_blocks_metrics_work_size",
     "wiu_blocks_metrics", "wiu3_metrics_size", "wiu3_workspace_bytes", "wiu3_metrics", "wiu3_rhs", "wiu3_cfl_dt",
@@ -110,6 +111,7 @@ def _load():
         "wiu_tuning_variants": (I, [I]),
         "wiu_set_tuning": (I, [I, I]),
         "wiu_get_tuning": (I, [I]),
+        "wiu_tuning_applies": (I, [G, I]),
         "wiu_profile_read": (I, [I, ctypes.POINTER(ctypes.c_longlong), ctypes.POINTER(ctypes.c_double)]),
     }
     for name, (res, args) in sig.items():
@@ -351,6 +353,14 @@ def set_tuning(direction, variant):
 
 def get_tuning(direction):
     return lib.wiu_get_tuning(int(direction))
+
+
+def tuning_applies(grid, scheme):
+    """Whether the sweeps, and with them the tile shapes, serve a single grid."""
+    v = lib.wiu_tuning_applies(ctypes.byref(grid), scheme_id(scheme))
+    if v < 0:
+        raise WiuError("invalid grid or scheme")
+    return bool(v)
 
 
 def profile_enable(on=True):

@@ -205,3 +205,15 @@ def test_3d_grids_and_options_are_validated(wiu):
     for cfl, scheme, n in ((0.0, 3, 2), (float("nan"), 3, 2), (0.5, 8, 2), (0.5, 3, 0), (0.5, 3, -1)):
         assert wiu.lib.wiu3_rk3_steps_cfl(ctypes.byref(g), scheme, ctypes.byref(P), dummy, dummy, cfl, n, dummy,
                                           dummy, None) == wiu.WIU_EINVAL
+
+
+def test_tuning_applies_to_grids_of_the_sweeps(wiu):
+    def applies(nx, ny, s="5-2MP"):
+        return wiu.tuning_applies(wiu.make_grid(nx, ny, ("periodic", "periodic"), (1.0, 1.0)), s)
+    assert not applies(256, 256) and applies(257, 256) and applies(7281, 9) and not applies(9, 7281)
+    assert not applies(8193, 1) and applies(8193, 1, "7-6MP") and not applies(8192, 1, "7-6MP")
+    bad = wiu.make_grid(0, 10, ("periodic", "periodic"), (1.0, 1.0))
+    assert wiu.lib.wiu_tuning_applies(ctypes.byref(bad), 3) == wiu.WIU_EINVAL
+    assert wiu.lib.wiu_tuning_applies(None, 3) == wiu.WIU_EINVAL
+    good = wiu.make_grid(10, 10, ("periodic", "periodic"), (1.0, 1.0))
+    assert wiu.lib.wiu_tuning_applies(ctypes.byref(good), 8) == wiu.WIU_EINVAL

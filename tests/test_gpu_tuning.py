@@ -58,3 +58,24 @@ def test_a_selection_that_is_put_back_is_the_first(wiu):
     finally:
         wiu.set_tuning(0, saved)
     assert (xi_tiles(wiu, *a), xi_tiles(wiu, *b)) == first
+
+
+def test_tuning_a_grid_of_stage_tiles_changes_nothing(wiu, tmp_path):
+    from paper_1810_11103_amd import autotune
+    cache = tmp_path / "tuning.json"
+    before = wiu.get_tuning(0), wiu.get_tuning(1)
+    sol, U = problem(wiu, 200, 180)
+    assert not wiu.tuning_applies(sol.grid, "5-2MP")
+    assert not any("sweep_kernel" in n for n in kernels(lambda: sol.rhs(U)))
+    try:
+        res = autotune.tune_single(sol, U, cache=str(cache))
+        assert tuple(res["variant"]) == before == (wiu.get_tuning(0), wiu.get_tuning(1))
+        assert res["ms"] > 0.0 and not cache.exists()
+        sol, U = problem(wiu, 300, 230)
+        assert wiu.tuning_applies(sol.grid, "5-2MP")
+        res = autotune.tune_single(sol, U, cache=str(cache))
+        assert tuple(res["variant"]) == (wiu.get_tuning(0), wiu.get_tuning(1))
+        assert len(res["all_ms"]) == wiu.tuning_variants(0) * wiu.tuning_variants(1) and cache.exists()
+    finally:
+        wiu.set_tuning(0, before[0])
+        wiu.set_tuning(1, before[1])
