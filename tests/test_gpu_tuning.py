@@ -79,3 +79,17 @@ def test_tuning_a_grid_of_stage_tiles_changes_nothing(wiu, tmp_path):
     finally:
         wiu.set_tuning(0, before[0])
         wiu.set_tuning(1, before[1])
+
+
+@pytest.mark.parametrize("s", ["3-1MP", "3-2MP", "5-1MP", "5-2MP", "7-1MP", "7-2MP", "7-4MP", "7-6MP"])
+def test_shape_of_a_batch_counts_the_lanes_that_run(wiu, s):
+    """The rule for a batch knows how many tiles either shape gives (128 lanes each)."""
+    blocks = []
+    for nx, ny in [(40, 31), (125, 24), (121, 17), (59, 30), (57, 9), (1, 5)]:
+        g = W.periodic_grid(nx, ny, (0, 10, 0, 10), A=0.1, seed=3)
+        blocks.append((g.x, g.y, g.bc, g.period))
+    for some in (blocks, blocks[1:2], blocks[2:3], blocks[4:5], blocks[5:]):
+        n = {v: wiu.BatchedPlan(some, s, xi_variant=v).info()[1] for v in (0, 2)}
+        plan = wiu.BatchedPlan(some, s)
+        assert plan.variant[0] == (2 if n[2] <= n[0] else 0), n
+        assert plan.info()[1] == min(n.values())
