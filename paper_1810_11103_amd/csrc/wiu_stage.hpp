@@ -41,7 +41,7 @@ template <int SC, int TX, int TY, bool OPT> struct StageLds {
 };
 
 // State at node (i, j) of the grid or beyond one of its sides (rules as in
-// sweep_tile): out of range in at most one direction.
+// sweep_tile; a single grid has no interfaces): out of range in at most one direction.
 WIU_DEV void stage_state(const SweepArgs& s, int i, int j, double Q[4]) {
   const Dims& d = s.d;
   const bool ox = i < 0 || i >= d.nx, oy = j < 0 || j >= d.ny;
@@ -52,13 +52,6 @@ WIU_DEV void stage_state(const SweepArgs& s, int i, int j, double Q[4]) {
     if (rule == 2) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) Q[c] = s.fixed[sd][c];
-      return;
-    }
-    if (rule == 3) {
-      const int m = min(k < 0 ? -k : k - n + 1, WIU_MB_REACH - 1);
-      const long long o = s.g0[sd] + m * s.gm[sd] + (ox ? j : i) * s.gl[sd];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) Q[c] = s.nbU[sd][c * s.nbnp[sd] + o];
       return;
     }
     const int kb = k < 0 ? 0 : n - 1;
@@ -83,8 +76,8 @@ WIU_DEV void stage_state(const SweepArgs& s, int i, int j, double Q[4]) {
   for (int c = 0; c < 4; ++c) Q[c] = s.U[c * d.np + o];
 }
 
-// Tile (bx, by); a block of NT threads, all of which call it.  `first`: this
-// workgroup writes the step size; clearing is shared by workgroup `wg` of `nwg`.
+// Tile (bx, by); a block of NT threads, all of which call it, once.  Workgroup 0 writes
+// the step size; clearing is shared by workgroup `wg` of `nwg`.
 template <int SC, int TX, int TY, int NT, bool OPT, bool PPM>
 WIU_DEV void stage_tile(const StageArgs& a, int bx, int by, int wg, int nwg, StageLds<SC, TX, TY, OPT>& L) {
   using T = Traits<SC>;
@@ -142,7 +135,6 @@ WIU_DEV void stage_tile(const StageArgs& a, int bx, int by, int wg, int nwg, Sta
   static_assert(NR <= 4, "rounds of tasks");
   const bool next = s.mode == 2 && s.nlam_xi;
 
-  __syncthreads();  // LDS of the previous tile is free
   // Everything the tile reads from global memory is loaded here, in one
   // latency: the metrics of this lane's tasks, states, line eigenvalues,
   // operands of the output nodes, the step size.
