@@ -1372,8 +1372,10 @@ Dims3 dims3(const wiu_grid3* g) {
   return d;
 }
 
-// Workspace: [status | line maxima, a ring of four sets (one per state) | dt | big area], the big area holding either the metric scratch
-// (inner derivatives, nodal band) or the stepping buffers (Racc, U1, U2).
+// Workspace: [status | line maxima, a ring of four sets (one per state) | dt | big
+// area], the big area holding either the metric scratch (inner derivatives, nodal band
+// and, on small grids, the extended coordinates) or the stepping buffers (Racc, U1, U2
+// and, below PAIR3_NODES, Reta).
 struct Ws3 {
   size_t lam, dt, big, metric_dx, metric_t, metric_x, racc, u1, u2, reta, total;
   long long nlam, set;  // words of a maxima set in use, and from one set to the next
@@ -1552,14 +1554,15 @@ int rc3(hipError_t e) { return e == hipSuccess ? WIU_OK : WIU_EHIP; }
 
 }  // namespace
 
-// nsteps TVD-RK3 steps; with cfl > 0 each at the CFL time step of its state,
-// written to dt[step] before the stages read it, otherwise all at the device
+// nsteps TVD-RK3 steps with cfl > 0, each at the CFL time step of its state,
+// written to dt[step] before the stages read it, or one step of the device
 // scalar *dt, only read.  Only the first step has a separate maxima pass: the
 // xi pass of each stage accumulates the next stage's maxima (that of the last
 // stage, for the next step, also the partial CFL maxima per j).
 static int rk3_3d(const wiu_grid3* g, int scheme, const wiu_params* p, double* U, const double* M, double cfl, double* dt,
            void* ws, wiu_stream_t stream, int nsteps = 1) {
-  if (!grid3_ok(g) || scheme < 0 || scheme > 7 || !params3_ok(p, scheme) || !U || !M || !dt || !ws || nsteps < 1)
+  if (!grid3_ok(g) || scheme < 0 || scheme > 7 || !params3_ok(p, scheme) || !U || !M || !dt || !ws || nsteps < 1 ||
+      (nsteps > 1 && !(cfl > 0.0)))
     return WIU_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   const Dims3 d = dims3(g);
