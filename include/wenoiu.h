@@ -207,8 +207,8 @@ int wiu_rk3_steps_cfl(const wiu_grid* g, int scheme, const wiu_params* p, double
  * For callers that cannot allocate device memory or pass a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  Same step and same results as wiu_rk3_step (the same
- * kernels), with its scratch (two sets of line maxima and two stage buffers,
- * wiu_noalloc_bytes() bytes) in one static device array of
+ * kernels), with its scratch (two sets of line maxima, or three on small grids,
+ * and two stage buffers, wiu_noalloc_bytes() bytes) in one static device array of
  * WIU_NOALLOC_SCRATCH_BYTES per device, which each device the library runs
  * on holds from the first call until the process ends; the call itself
  * allocates nothing.  Grids whose scratch exceeds the array (beyond about
@@ -455,14 +455,19 @@ int wiu_set_tuning(int dir, int variant);
 int wiu_get_tuning(int dir);
 int wiu_tuning_applies(const wiu_grid* g, int scheme);
 
-/* Kernel timing for benchmarks.  While enabled, every launch of the
- * library's kernels is bracketed by HIP events recorded on its launch stream.
+/* Kernel timing for benchmarks.  While enabled, the launches of the kernels
+ * named below are bracketed by HIP events recorded on their launch stream.
  * wiu_profile_read() synchronises the device, returns the number of launches
  * and their mean duration in milliseconds for kernel `id` (WIU_K_*), and
  * clears that kernel's records. */
 enum {
-  WIU_K_WAVE_MAX = 0, WIU_K_SWEEP_XI = 1, WIU_K_SWEEP_ETA = 2, WIU_K_METRICS = 3,
-  WIU_K_SWEEP3 = 4,  /* 3-D direction pass */
+  WIU_K_WAVE_MAX = 0, WIU_K_SWEEP_XI = 1,
+  WIU_K_SWEEP_ETA = 2,  /* eta sweep; on a grid that the sweeps do not serve
+                           (wiu_tuning_applies) a launch of both directions' tiles,
+                           beside which there is no xi sweep */
+  WIU_K_METRICS = 3,
+  WIU_K_SWEEP3 = 4,  /* 3-D direction pass; below 2^21 nodes the zeta and eta
+                        passes are one launch */
   WIU_K_COUNT = 5
 };
 int wiu_profile_enable(int on);

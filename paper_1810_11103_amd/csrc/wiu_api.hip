@@ -266,9 +266,10 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? WIU_OK : WIU_EHIP; }
 
 // Residual pieces shared by rhs and the RK stages: line maxima, then on small
 // grids one launch of stage tiles (wiu_stage.hpp), on others the xi sweep into
-// R^xi and the eta sweep with the requested epilogue.  The maxima are computed here unless given (lx_in/le_in, accumulated by the
-// previous stage); with nlx/nle (mode 2 only) the eta sweep accumulates the
-// maxima of the new stage state there.
+// R^xi and the eta sweep with the requested epilogue.  The maxima are computed here
+// unless given (lx_in/le_in, accumulated by the previous stage); with nlx/nle (mode 2
+// only) the stage tiles or the eta sweep accumulate the maxima of the new stage state
+// there.
 struct Maxima {
   const unsigned long long *lx_in = nullptr, *le_in = nullptr;
   unsigned long long *nlx = nullptr, *nle = nullptr;
