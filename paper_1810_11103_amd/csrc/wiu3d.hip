@@ -927,8 +927,9 @@ template <int SC, int DIR, int NA, int NB, bool OPT = false> struct Sweep3Lds {
 // (nodal flux at k and both side fluxes at k + 1/2), then the first OUT
 // lanes of each line form H_{i+1/2} - H_{i-1/2} and, by `mode`: 0 Racc = R;
 // 1 Racc += R; 2 dU/dt = -(Racc + R)/J^{-1}; 3 the RK stage
-// U_out = ca U0 + cb (U + dt dU/dt); the xi pass adds Reta to Racc when that is set.  Four block-wide barriers on every path
-// (five in an xi pass that accumulates the next stage's maxima).
+// U_out = ca U0 + cb (U + dt dU/dt); the xi pass adds Reta to Racc when that is set.
+// Four block-wide barriers on every path (five in an xi pass that accumulates the next
+// stage's maxima).
 // OPT: compiled with the scheme options (a.vars, a.ah, a.weights); without
 // it the sweep runs the paper's configuration and carries no code for them, and
 // PPM says whether the weights are mapped.

@@ -202,8 +202,8 @@ WIU_DEV void fused_stage_out(const SweepArgs& s, SweepLds<SC, 1, NA, NB, OPT>& L
 // the mapping is compiled in (or out) too: asked in every interpolation it cut
 // the fluxes into blocks that the compiler could not schedule across and held
 // 20 registers more.  With the shorter interpolation (weno5): 2048^2 WENOIU5-2MP,
-// two steps 2741 -> 2650 us and 1235 -> 1040 VALU instructions an item of the xi
-// sweep; 1000 x 760 WENOIU7-4MP, one step 414 -> 385 us.
+// two steps 2741 -> 2650 us and 1139 -> 1040 VALU instructions an item of the xi
+// sweep, 1235 -> 1134 of the eta sweep; 1000 x 760 WENOIU7-4MP, one step 414 -> 385 us.
 template <int SC, int DIR, int NA, int NB, bool OPT, bool PPM>
 WIU_DEV void sweep_tile(const SweepArgs& s, int bxl, int byl, SweepLds<SC, DIR, NA, NB, OPT>& L) {
   const double ah = OPT ? s.ah : 1.0;
