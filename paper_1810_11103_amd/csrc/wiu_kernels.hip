@@ -315,8 +315,7 @@ __global__ void __launch_bounds__(256) wave_max_kernel(Dims d, const double* __r
 }
 
 __global__ void fill_u64_kernel(unsigned long long* p, long long n, unsigned long long v) {
-  long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) p[t] = v;
+  for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < n; t += (long long)gridDim.x * 256) p[t] = v;
 }
 
 __global__ void cfl_dt_kernel(const unsigned long long* cfl_max, double cfl, double* dt) {
@@ -432,8 +431,11 @@ hipError_t launch_wave_max(const Dims& d, const double* U, const double* M, doub
   return hipGetLastError();
 }
 
+// A launch holds fewer than 2^32 threads, and the records of many steps of a long strip
+// more words than that: beyond 2^22 blocks a thread clears several.
 hipError_t launch_fill_u64(unsigned long long* p, long long n, hipStream_t st) {
-  hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n, 0ull);
+  const long long blocks = (n + 255) / 256, most = 1LL << 22;
+  hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)(blocks < most ? blocks : most)), dim3(256), 0, st, p, n, 0ull);
   return hipGetLastError();
 }
 
