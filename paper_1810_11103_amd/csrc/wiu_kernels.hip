@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(MT_THREADS) metrics_kernel(Dims d, MetricStenc
   __shared__ LT L;
   const int lid = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
   const int a0 = (lid % gridDim.x) * MT_X - GHOST, b0 = (lid / gridDim.x) * MT_Y - GHOST;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x + MT_X * threadIdx.y;
   if (lid == 0 && tid == 0) {
     double* tag = M + 9 * d.mplane;
     tag[0] = TAG_MAGIC; tag[1] = (double)scheme; tag[2] = (double)d.nx; tag[3] = (double)d.ny;
@@ -445,10 +445,11 @@ hipError_t launch_metrics(const Dims& d, int scheme, double ah, const double* x,
   int K = METRIC_REACH;
   while (K > (scheme >= 4 ? 4 : 3) && ms.d[K - 1] == 0.0) --K;
   const dim3 grid((d.nx + 2 * GHOST + MT_X - 1) / MT_X, (d.ny + 2 * GHOST + MT_Y - 1) / MT_Y);
+  // as many threads along x as nodes: a launch wraps at 2^32 of them per direction
+  const dim3 block(MT_X, MT_THREADS / MT_X);
 #define WIU_M2(k, eight)                                                                                     \
   if (K == k && (scheme >= 4) == eight)                                                                      \
-    hipLaunchKernelGGL((metrics_kernel<k, eight>), grid, dim3(MT_THREADS), 0, st, d, ms, scheme, ah, x, y, M, \
-                       status);
+    hipLaunchKernelGGL((metrics_kernel<k, eight>), grid, block, 0, st, d, ms, scheme, ah, x, y, M, status);
   WIU_M2(3, false) WIU_M2(4, false) WIU_M2(4, true) WIU_M2(5, true) WIU_M2(6, true) WIU_M2(7, true)
 #undef WIU_M2
   return hipGetLastError();
